@@ -6,7 +6,8 @@ keeps the fastest and caches the choice per (GPU, grid, domain, control kind)
 in a JSON file, so later contexts of the same shape skip the timing.  A
 candidate is (T, H, tw, th): T time steps per launch; H rows per wave of the
 wave-strip kernel (periodic, uniform material) or, with tw, th > 0, a tw x th
-tile of the LDS-tiled kernel (any problem); T = 1 is one step per launch.
+tile of the LDS-tiled kernel (any problem); T = 1 is one step per launch, T = -1
+the library's automatic shape.
 Plates and E-field controls only take tiled or single-step shapes.  The timed
 sweeps advance the context's current state; call it before a solve
 (primal_solve resets the state).
@@ -26,7 +27,9 @@ STRIP = ((8, 24, 0, 0), (8, 32, 0, 0), (8, 48, 0, 0), (8, 64, 0, 0), (8, 96, 0, 
 TILES = ((8, 0, 16, 16), (6, 0, 20, 20), (4, 0, 24, 24), (6, 0, 52, 4), (8, 0, 8, 8), (8, 0, 12, 12),
          (3, 0, 26, 26), (5, 0, 22, 22))
 SINGLE = ((1, 0, 0, 0),)
-CANDIDATES = STRIP + TILES + SINGLE
+# the library's own choice: register panels where their regions fit the compute units in one round
+AUTO = ((-1, 0, 0, 0),)
+CANDIDATES = AUTO + STRIP + TILES + SINGLE
 TIE = 0.02
 CACHE = os.environ.get("SLBM_TUNE_CACHE", os.path.join(os.path.expanduser("~"), ".cache", "slbm_autotune.json"))
 
@@ -54,7 +57,7 @@ def _key(ctx, problem, device):
     # the candidate set is part of the key: a cached choice from another set is not reused
     cands = len(STRIP), len(TILES), len(SINGLE)
     return (f"{device}|{problem['nx']}x{problem['ny']}|dom{problem.get('domain', 0)}"
-            f"|ctrl{problem.get('control_kind', 0)}|cand{cands[0]}.{cands[1]}.{cands[2]}")
+            f"|ctrl{problem.get('control_kind', 0)}|cand{cands[0]}.{cands[1]}.{cands[2]}.{len(AUTO)}")
 
 
 def device_key():
@@ -91,7 +94,7 @@ def autotune(ctx, problem, control, sweeps=96, device=None, use_cache=True, cand
     `device` names the GPU in the cache key (default: device_key())."""
     key = _key(ctx, problem, device_key() if device is None else device)
     if candidates is None:
-        candidates = (TILES + SINGLE) if _tiled_only(problem) else CANDIDATES
+        candidates = (AUTO + TILES + SINGLE) if _tiled_only(problem) else CANDIDATES
     cache = _load() if use_cache else {}
     if key in cache and "tiles" in cache[key]:
         e = cache[key]
@@ -101,7 +104,7 @@ def autotune(ctx, problem, control, sweeps=96, device=None, use_cache=True, cand
     times = {}
     for c in candidates:
         _apply(ctx, c)
-        T = max(c[0], 1)
+        T = 8 if c[0] < 0 else max(c[0], 1)
         n = max(sweeps // T, 1) * T
         S.solid_lbm_time_sweeps(ctx, 0, T * 2)               # warm-up of this shape
         times[c] = S.solid_lbm_time_sweeps(ctx, 0, n) / n * 1e3

@@ -14,7 +14,7 @@
 #include <vector>
 
 #include "solid_lbm.h"
-#include "slbm_kernels.h"
+#include "slbm_panel.h"
 
 using namespace slbm;
 
@@ -318,9 +318,9 @@ struct CheckLog {
 // fused kernels cover the periodic, uniform-material bulk.
 // The LDS-tiled kernel serves plates and E fields always, periodic uniform
 // problems when a tile shape was set, and, with automatic tuning, periodic
-// uniform grids up to 131072 nodes (measured on MI355X: 128^2 1.3 vs 3.5 us
-// per step, 256^2 1.7 vs 3.9 for the best wave-strip shape; from 512^2 on the
-// wave strips are faster).
+// uniform grids up to 131072 nodes that the register panels (panel_shape) do
+// not take (measured on MI355X: 128^2 1.3 vs 3.5 us per step, 256^2 1.7 vs 3.9
+// for the best wave-strip shape).
 constexpr int64_t kTileAutoMaxNodes = 131072;
 bool use_tiles(const slbm_ctx* c)
 {
@@ -591,6 +591,106 @@ void launch_tile(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, int h
 #undef TL_CASE
 }
 
+// ---------------------------------------------------------------- register panels
+typedef void (*panel_fn)(PanelArgs);
+template <bool E, bool A>
+panel_fn panel_of(int R)
+{
+    switch (R) {
+        case 3: return k_sweep_panel<E, A, 3>;
+        case 4: return k_sweep_panel<E, A, 4>;
+        case 6: return k_sweep_panel<E, A, 6>;
+        default: return E ? nullptr : k_sweep_panel<false, A, 8>;
+    }
+}
+
+// The fused launches of a solve loop.
+struct Fuse {
+    int T = 1;        // steps per wave-strip launch
+    int TL = 1;       // steps per launch of LDS tiles or panels
+    int R = 0;        // rows per lane of the panels (0: LDS tiles)
+};
+
+int panel_tiles(const slbm_ctx* c, int R, int h)
+{
+    const int tw = 64 - 2 * h, th = kPanelWaves * R - 2 * h;
+    return ((c->nx + tw - 1) / tw) * ((c->ny + th - 1) / th);
+}
+
+// Automatic panel shape of a periodic problem.  A workgroup fills a compute
+// unit, so a shape is good while its regions fit the compute units in one
+// round.  The shapes in order of their time per step in one round (us per
+// step, uniform material, 100 - 250 workgroups): (R, h) = (3, 6) 1.6, (4, 8)
+// 1.7, (4, 7) 1.85, (6, 12) 1.88, (6, 10) 2.1, (8, 12) 2.4, (6, 8) 2.4, (8, 8)
+// 3.0; the first that fits is taken.  Grids whose 16 x 16 LDS tiles fit in one
+// round keep those (256^2: 1.32 against 1.54 with (3, 6)).  Beyond one round
+// uniform problems take the wave strips (800^2: 4.14 us per step against 4.25
+// with panels of (8, 7) and 4.6 in several rounds; 1024^2: 5.2 against 6.5).
+// E fields have no strips and go on with (3, 6) in several rounds.  (8, h)
+// spills with a modulus per node, so E fields do not take it.
+bool panel_shape(const slbm_ctx* c, Fuse* f)
+{
+    if (c->masked || c->tb_T >= 0 || c->tile_w > 0) return false;
+    const int cus = c->simds / 4;
+    if ((int64_t)((c->nx + 15) / 16) * ((c->ny + 15) / 16) <= cus) return false;
+    static const int shapes[8][2] = {{3, 6}, {4, 8}, {4, 7}, {6, 12}, {6, 10}, {8, 12}, {6, 8}, {8, 8}};
+    for (const auto& s : shapes) {
+        if (c->efield_on && s[0] == 8) continue;
+        if (panel_tiles(c, s[0], s[1]) > cus) continue;
+        f->R = s[0];
+        f->TL = s[1];
+        f->T = 1;
+        return true;
+    }
+    if (!c->efield_on) return false;
+    f->R = 3;
+    f->TL = 6;
+    f->T = 1;
+    return true;
+}
+
+void launch_panel(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, const Fuse& f)
+{
+    PanelArgs a;
+    a.src = s.src;
+    a.dst = s.dst;
+    a.g = s.g;
+    a.E = s.E;
+    a.status = s.status;
+    a.nx = c->nx;
+    a.ny = c->ny;
+    a.N = c->N;
+    a.k11 = s.k11;
+    a.ks = s.ks;
+    a.kd = s.kd;
+    a.nu = s.nu;
+    a.scale = s.scale;
+    a.halo = f.TL;
+    a.steps = steps;
+    a.tiles_x = (c->nx + 63 - 2 * f.TL) / (64 - 2 * f.TL);
+    const panel_fn fn = c->efield_on ? (adjoint ? panel_of<true, true>(f.R) : panel_of<true, false>(f.R))
+                                     : (adjoint ? panel_of<false, true>(f.R) : panel_of<false, false>(f.R));
+    hipLaunchKernelGGL(fn, dim3((unsigned)panel_tiles(c, f.R, f.TL)), dim3(kPanelBlock), 0, c->stream, a);
+}
+
+// Chooses the fused launches of a loop and builds what they need.
+int plan_fuse(slbm_ctx* c, Fuse* f)
+{
+    if (panel_shape(c, f)) return SLBM_OK;
+    f->T = fused_steps(c);
+    f->TL = tile_steps(c);
+    int rc;
+    if (f->TL > 1 && c->masked && (rc = tile_lds_limits(c))) return rc;
+    if (f->TL > 1 && (rc = ensure_tile_plan(c, f->TL))) return rc;
+    return SLBM_OK;
+}
+
+void launch_region(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, const Fuse& f)
+{
+    if (f.R > 0) launch_panel(c, adjoint, s, steps, f);
+    else launch_tile(c, adjoint, s, steps, f.TL);
+}
+
 // ---------------------------------------------------------------- tangent solves
 int64_t control_len(const slbm_ctx* c);
 int dot(slbm_ctx* c, const double* a, const double* w, int64_t n, double* out_host);
@@ -798,16 +898,12 @@ int run_loop(slbm_ctx* c, bool adjoint, int start, int64_t last, bool use_tol, i
     // buffer holding the input of sweep s; check sweeps and the final sweep are
     // single-step launches, runs of plain sweeps between them are fused by T
     int cur = start;
-    const int T = fused_steps(c);
-    const int TL = tile_steps(c);
-    if (TL > 1 && c->masked) {
-        int rc = tile_lds_limits(c);
+    Fuse fuse;
+    {
+        int rc = plan_fuse(c, &fuse);
         if (rc) return rc;
     }
-    if (TL > 1) {
-        int rc = ensure_tile_plan(c, TL);
-        if (rc) return rc;
-    }
+    const int T = fuse.T, TL = fuse.TL;
     CheckLog checks;                              // (step, input buffer) of the latest check sweeps
     int last_in = start;
     auto last_report = std::chrono::steady_clock::now();
@@ -832,7 +928,7 @@ int run_loop(slbm_ctx* c, bool adjoint, int start, int64_t last, bool use_tol, i
                 a.src = bufs[cur];
                 a.dst = bufs[cur ^ 1];
                 HIPCHK(c, c->lt.before(c->stream, k, s));
-                launch_tile(c, adjoint, a, k, TL);
+                launch_region(c, adjoint, a, k, fuse);
                 cur ^= 1;
                 s += k;
                 continue;
@@ -1623,16 +1719,12 @@ int solid_lbm_time_sweeps(slbm_ctx* c, int32_t adjoint, int64_t n, double* ms)
     a.scale = c->dx2 / c->cbar;
     double** bufs = adjoint ? c->abuf : c->fbuf;
     int cur = adjoint ? c->adj_cur : c->prim_cur;
-    const int T = fused_steps(c);
-    const int TL = tile_steps(c);
-    if (TL > 1 && c->masked) {
-        int rc = tile_lds_limits(c);
+    Fuse fuse;
+    {
+        int rc = plan_fuse(c, &fuse);
         if (rc) return rc;
     }
-    if (TL > 1) {
-        int rc = ensure_tile_plan(c, TL);
-        if (rc) return rc;
-    }
+    const int T = fuse.T, TL = fuse.TL;
     HIPCHK(c, hipEventRecord(c->t0, c->stream));
     for (int64_t s = 0; s < n;) {
         a.src = bufs[cur];
@@ -1642,7 +1734,7 @@ int solid_lbm_time_sweeps(slbm_ctx* c, int32_t adjoint, int64_t n, double* ms)
             s += T;
         } else if (TL > 1 && n - s >= 2) {
             const int k = (int)std::min<int64_t>(n - s, TL);
-            launch_tile(c, adjoint != 0, a, k, TL);
+            launch_region(c, adjoint != 0, a, k, fuse);
             s += k;
         } else {
             launch_sweep(c, adjoint != 0, a, false);
