@@ -48,6 +48,18 @@ int slbm_conv3x3_backward_weight(const float *dz, const uint16_t *x, float *dw, 
                                  int32_t Cin, int32_t Cout, int32_t H, int32_t W, int32_t dilation,
                                  void *stream);
 
+/* The same with a workspace: the pixels are split over the device's compute
+ * units, each writes its partial sums to ws (device memory, ws_bytes of it,
+ * not kept after the call; slbm_conv3x3_backward_weight_workspace gives the
+ * bytes a layer takes, 0 if it has no such split: over 56 input channels, or
+ * a dilation whose input region exceeds the LDS), and a second kernel adds
+ * them in a fixed order.  With ws NULL or too small it is
+ * slbm_conv3x3_backward_weight. */
+int64_t slbm_conv3x3_backward_weight_workspace(int32_t B, int32_t Cin, int32_t H, int32_t W, int32_t dilation);
+int slbm_conv3x3_backward_weight_ws(const float *dz, const uint16_t *x, float *dw, float *db, int32_t B,
+                                    int32_t Cin, int32_t Cout, int32_t H, int32_t W, int32_t dilation, void *ws,
+                                    int64_t ws_bytes, void *stream);
+
 /* dz = dy * (y > 0) (ReLU backward; relu == 0: dz = dy), also as bf16. n elements. */
 int slbm_act_backward(const float *dy, const float *y, float *dz, uint16_t *dz_bf16, int64_t n,
                       int32_t relu, void *stream);

@@ -72,6 +72,9 @@ _P = ctypes.c_void_p
 _i32, _i64, _f32 = ctypes.c_int32, ctypes.c_int64, ctypes.c_float
 _L.slbm_conv3x3_forward.argtypes = [_P, _P, _P, _P, _P, _i32, _i32, _i32, _i32, _i32, _i32, _i32, _P]
 _L.slbm_conv3x3_backward_weight.argtypes = [_P, _P, _P, _P, _i32, _i32, _i32, _i32, _i32, _i32, _P]
+_L.slbm_conv3x3_backward_weight_ws.argtypes = [_P, _P, _P, _P, _i32, _i32, _i32, _i32, _i32, _i32, _P, _i64, _P]
+_L.slbm_conv3x3_backward_weight_workspace.argtypes = [_i32, _i32, _i32, _i32, _i32]
+_L.slbm_conv3x3_backward_weight_workspace.restype = _i64
 _L.slbm_act_backward.argtypes = [_P, _P, _P, _P, _i64, _i32, _P]
 _L.slbm_pack_weights.argtypes = [_P, _P, _P, _i32, _i32, _P]
 _L.slbm_to_bf16.argtypes = [_P, _P, _i64, _P]
@@ -136,6 +139,9 @@ class ConvNet:
         B, _, H, W = self.acts[0].shape
         _need(dy, torch.float32, (B, self.layers[-1][1], H, W), "output gradient")
         self.gw, self.gb = [None] * len(self.layers), [None] * len(self.layers)
+        # partial sums of the weight gradients: one buffer for all layers (they run one after another)
+        nws = max(_L.slbm_conv3x3_backward_weight_workspace(B, ci, H, W, dil) for ci, _, _, dil in self.layers)
+        ws = torch.empty(nws, dtype=torch.uint8, device="cuda")
         for i in range(len(self.layers) - 1, -1, -1):
             ci, co, relu, dil = self.layers[i]
             dz = torch.empty_like(dy)
@@ -144,8 +150,8 @@ class ConvNet:
                                       _stream()), "act backward")
             gw = torch.empty((co, ci * 9), dtype=torch.float32, device="cuda")
             gb = torch.empty(co, dtype=torch.float32, device="cuda")
-            _chk(_L.slbm_conv3x3_backward_weight(_p(dz), _p(self.acts[i]), _p(gw), _p(gb), B, ci, co, H, W, dil,
-                                                 _stream()), "weight gradient")
+            _chk(_L.slbm_conv3x3_backward_weight_ws(_p(dz), _p(self.acts[i]), _p(gw), _p(gb), B, ci, co, H, W, dil,
+                                                    _p(ws), nws, _stream()), "weight gradient")
             self.gw[i], self.gb[i] = gw, gb
             if i > 0:
                 dx = torch.empty((B, ci, H, W), dtype=torch.float32, device="cuda")
