@@ -812,33 +812,22 @@ __device__ __forceinline__ int xcd_order(int b, int n)
 }
 
 // Whole-wave lane shifts of a double: up = value of lane l-1, down = value of
-// lane l+1 (the end lanes keep their own value; they are halo lanes).
-// DPP wave_shr:1 / wave_shl:1 moves (no LDS crossbar) unless built with
-// SLBM_TB_DPP=0 (then ds_bpermute shuffles).
-#ifndef SLBM_TB_DPP
-#define SLBM_TB_DPP 1
-#endif
+// lane l+1 (the end lane gets 0; end lanes are halo lanes).  DPP wave_shr:1 /
+// wave_shl:1 moves, no LDS crossbar.  bound_ctrl zero-fills, so that the move
+// needs no copy of its source into its destination first: with the end lane
+// keeping its own value every shift cost two moves per half (24 of 62 VALU
+// instructions per node-step in the wave strips, 12 of 50 now).
 __device__ __forceinline__ double lane_up(double v)
 {
-#if SLBM_TB_DPP
-    int lo = __double2loint(v), hi = __double2hiint(v);
-    lo = __builtin_amdgcn_update_dpp(lo, lo, 0x138, 0xf, 0xf, false);  // wave_shr:1
-    hi = __builtin_amdgcn_update_dpp(hi, hi, 0x138, 0xf, 0xf, false);
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x138, 0xf, 0xf, true);  // wave_shr:1
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x138, 0xf, 0xf, true);
     return __hiloint2double(hi, lo);
-#else
-    return __shfl_up(v, 1);
-#endif
 }
 __device__ __forceinline__ double lane_down(double v)
 {
-#if SLBM_TB_DPP
-    int lo = __double2loint(v), hi = __double2hiint(v);
-    lo = __builtin_amdgcn_update_dpp(lo, lo, 0x130, 0xf, 0xf, false);  // wave_shl:1
-    hi = __builtin_amdgcn_update_dpp(hi, hi, 0x130, 0xf, 0xf, false);
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x130, 0xf, 0xf, true);  // wave_shl:1
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x130, 0xf, 0xf, true);
     return __hiloint2double(hi, lo);
-#else
-    return __shfl_down(v, 1);
-#endif
 }
 
 __device__ __forceinline__ int wrapi(int v, int n)
