@@ -274,13 +274,14 @@ int solid_lbm_time_sweeps(slbm_ctx *ctx, int32_t adjoint, int64_t n, double *ms)
  * launch: 2, 4, 6 or 8 for periodic, uniform-material problems (wave-strip
  * kernel), 2 .. 8 for plates, E-field controls and problems given a tile by
  * solid_lbm_set_tiles (LDS-tiled kernel).  Automatic: the LDS-tiled kernel
- * for plates (8 steps up to 131072 nodes; above, the most of 6, 5, 4, 3 steps
- * whose (32 - 2 steps)^2 tiles number no more than the device's compute
- * units, else 6) and for periodic grids whose 16 x 16 tiles fit the compute
- * units at once (8 steps); larger periodic grids take register panels of 64
- * columns (6 .. 12 steps) while a shape of them fits the compute units at
- * once, and, with a uniform material, the wave-strip kernel with 8 steps
- * beyond, with as many rows per wave as keep the wave count at or
+ * with 8 steps for plates and periodic grids whose 16 x 16 tiles fit the
+ * compute units at once; larger plates take register panels of 64 columns (6,
+ * 8 or 10 steps, by a model of the launch; a plate whose rim is too dense for
+ * them the LDS tiles: 8 steps up to 131072 nodes, above the most of 6, 5, 4, 3
+ * whose (32 - 2 steps)^2 tiles number no more than the compute units, else 6);
+ * larger periodic grids take register panels (6 .. 12 steps) while a shape of
+ * them fits the compute units at once, and, with a uniform material, the
+ * wave-strip kernel with 8 steps beyond, with as many rows per wave as keep the wave count at or
  * below the device's SIMD count.  rows_per_wave: rows each wave of a wave-strip launch
  * covers (0 = automatic).  Every setting gives the same result bit for bit:
  * a fused launch performs exactly the arithmetic of its single sweeps.

@@ -145,6 +145,7 @@ struct slbm_ctx {
     int kind = 0, nmodes = 0, project = 0, normalize = 1;
     bool masked = false;
     int nb = 0;  // boundary records
+    std::vector<int32_t> bcells;  // their cells
     double cbar = 1.0;
     hipStream_t stream = nullptr;
     // device buffers
@@ -180,6 +181,14 @@ struct slbm_ctx {
     int32_t* plan_nst = nullptr;
     int64_t plan_cap = 0;        // tiles
     int plan_key[4] = {0, 0, 0, 0};   // tw, th, halo, order of the plan held (tw = 0: none)
+    // launch plan of a plate's panels (k_panel_plan), for launches of several steps
+    int2* pplan = nullptr;
+    double* pplan_coef = nullptr;
+    int32_t* pplan_n = nullptr;
+    int32_t* ptiles = nullptr;
+    std::vector<int32_t> plive;  // tiles with domain nodes, by workgroup
+    std::vector<uint8_t> mask;   // plates: node_mask
+    int pshape[2] = {-1, 0};     // rows per lane (-1: not looked for yet, 0: no panels), halo
     int64_t nblk = 0;  // blocks of one sweep
     int64_t pcap = 0;  // capacity of the partial-sum buffer in blocks
     // state
@@ -604,6 +613,29 @@ panel_fn panel_of(int R)
     }
 }
 
+template <bool E, bool A>
+panel_fn plate_of(int R)
+{
+    switch (R) {
+        case 3: return k_sweep_plate<E, A, 3>;
+        default: return k_sweep_plate<E, A, 4>;
+    }
+}
+panel_fn panel_kernel(bool masked, bool efield, bool adjoint, int R)
+{
+    switch ((masked ? 4 : 0) | (efield ? 2 : 0) | (adjoint ? 1 : 0)) {
+        case 0: return panel_of<false, false>(R);
+        case 1: return panel_of<false, true>(R);
+        case 2: return panel_of<true, false>(R);
+        case 3: return panel_of<true, true>(R);
+        case 4: return plate_of<false, false>(R);
+        case 5: return plate_of<false, true>(R);
+        case 6: return plate_of<true, false>(R);
+        default: return plate_of<true, true>(R);
+    }
+}
+constexpr size_t kPlateLds = (kPanelEdge + 8 * kPanelCap) * sizeof(double);
+
 // The fused launches of a solve loop.
 struct Fuse {
     int T = 1;        // steps per wave-strip launch
@@ -653,6 +685,7 @@ bool panel_shape(const slbm_ctx* c, Fuse* f)
 void launch_panel(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, const Fuse& f)
 {
     PanelArgs a;
+    std::memset(&a, 0, sizeof(a));
     a.src = s.src;
     a.dst = s.dst;
     a.g = s.g;
@@ -669,14 +702,190 @@ void launch_panel(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, cons
     a.halo = f.TL;
     a.steps = steps;
     a.tiles_x = (c->nx + 63 - 2 * f.TL) / (64 - 2 * f.TL);
-    const panel_fn fn = c->efield_on ? (adjoint ? panel_of<true, true>(f.R) : panel_of<true, false>(f.R))
-                                     : (adjoint ? panel_of<false, true>(f.R) : panel_of<false, false>(f.R));
-    hipLaunchKernelGGL(fn, dim3((unsigned)panel_tiles(c, f.R, f.TL)), dim3(kPanelBlock), 0, c->stream, a);
+    a.code = s.code;
+    a.bnodes = s.bnodes;
+    a.E0 = s.E0;
+    unsigned wgs = (unsigned)panel_tiles(c, f.R, f.TL);
+    if (c->masked) {
+        wgs = (unsigned)c->plive.size();
+        a.plan = c->pplan;
+        a.plan_coef = c->pplan_coef;
+        a.plan_n = c->pplan_n;
+        a.tiles = c->ptiles;
+    }
+    hipLaunchKernelGGL(panel_kernel(c->masked, c->efield_on, adjoint, f.R), dim3(wgs),
+                       dim3(c->masked ? kPlateBlock : kPanelBlock), c->masked ? kPlateLds : 0, c->stream, a);
+}
+
+// Tiles of a plate's panel shape that write at least one domain node, in the
+// order of the workgroups that run them.
+struct PlateTiles {
+    std::vector<int32_t> list;
+    int rim = 0;      // tiles with boundary nodes in their region
+    int most = 0;     // most boundary nodes of a region (halo and periodic copies included)
+};
+
+PlateTiles plate_tiles(const slbm_ctx* c, int R, int h)
+{
+    const int tw = 64 - 2 * h, th = kPanelWaves * R - 2 * h;
+    const int tx = (c->nx + tw - 1) / tw, ty = (c->ny + th - 1) / th;
+    // tiles whose region holds coordinate v, periodic copies one by one
+    auto spans = [](int v, int n, int t, int size, int h, int tiles, std::vector<int>& out) {
+        out.clear();
+        for (int u = v - ((v + h) / n) * n; u < tiles * t + size; u += n)
+            for (int b = std::max(0, (u + h - size) / t); b < tiles && b * t - h <= u; ++b)
+                if (u < b * t - h + size) out.push_back(b);
+    };
+    std::vector<int> count((size_t)tx * ty, 0), bx, by;
+    PlateTiles out;
+    int row = -1;
+    for (int32_t n : c->bcells) {                        // in row-major order
+        if (n / c->nx != row) spans(row = n / c->nx, c->ny, th, kPanelWaves * R, h, ty, by);
+        spans(n % c->nx, c->nx, tw, 64, h, tx, bx);
+        for (int j : by)
+            for (int i : bx) out.most = std::max(out.most, ++count[(size_t)j * tx + i]);
+    }
+    for (int j = 0; j < ty; ++j)
+        for (int i = 0; i < tx; ++i) {
+            bool live = false;
+            for (int y = j * th; y < std::min((j + 1) * th, c->ny) && !live; ++y) {
+                const uint8_t* m = c->mask.data() + (int64_t)y * c->nx;
+                live = std::any_of(m + i * tw, m + std::min((i + 1) * tw, c->nx), [](uint8_t v) { return v != 0; });
+            }
+            if (live) out.list.push_back(j * tx + i);
+        }
+    // Workgroup b runs entry xcd_order(b) of the list, which hands XCD x one run
+    // of it.  Each run gets its share of the slow rim tiles first, then of the
+    // inner tiles, both contiguous in the grid: no XCD has more rim tiles than
+    // the others, and its last round is made of inner tiles.
+    std::vector<int32_t> rim, inner;
+    for (int32_t t : out.list) (count[t] ? rim : inner).push_back(t);
+    const size_t n = out.list.size(), nr = rim.size();
+    out.rim = (int)nr;
+    size_t ri = 0, ii = 0, at = 0;
+    for (size_t x = 0; x < kXcds; ++x) {
+        const size_t len = n / kXcds + (x < n % kXcds ? 1 : 0);
+        size_t r = nr / kXcds + (x < nr % kXcds ? 1 : 0);
+        r = std::min(r, len);
+        if (x == kXcds - 1) r = nr - ri;                 // what is left fits: at + len = n
+        for (size_t k = 0; k < len; ++k) out.list[at++] = k < r ? rim[ri++] : inner[ii++];
+    }
+    return out;
+}
+
+// Time of one launch of n equal shares (one per XCD) of rim and inner tiles on
+// m compute units each: rim tiles first, then inner tiles as units come free.
+double plate_launch_us(int rims, int inners, int m, double tr, double ti)
+{
+    std::vector<double> unit(m, 0.0);
+    auto run = [&](double t) {
+        auto u = std::min_element(unit.begin(), unit.end());
+        *u += t;
+    };
+    for (int k = 0; k < rims; ++k) run(tr);
+    for (int k = 0; k < inners; ++k) run(ti);
+    return *std::max_element(unit.begin(), unit.end());
+}
+
+// Automatic panel shape of a plate (found once per context: it depends on the
+// geometry only).  Plates whose 16 x 16 LDS tiles fit the compute units in one
+// round keep those (250 x 150: 2.04 us per primal step against 2.2 for the best
+// panels).  Beyond, the shape of least time by plate_launch_us, with tile times
+// fitted to E-field plates from 64 x 39 to 1000 x 600 (us): with boundary nodes
+// 8 + 1.53 h and 12.3 + 1.73 h for R = 3 and 4 rows per lane, without 5 + 0.7 h
+// and 6.5 + 0.91 h.  It takes the fastest of the shapes at every size measured
+// (us per primal step, fastest and slowest of the five): 384 x 231 (3, 8) 2.57
+// - 3.56, 512 x 308 (3, 8) 2.65 - 3.73, 700 x 420 (4, 8) 3.42 - 4.57, 850 x 510
+// (4, 6) 4.29 - 5.69, 1000 x 600 (4, 6) 5.81 - 7.64.  R = 2 is slower
+// throughout.  A region must not hold more boundary nodes than the boundary
+// waves have lanes; plates with denser rims keep the LDS tiles.
+bool plate_shape(slbm_ctx* c, Fuse* f)
+{
+    if (c->tb_T >= 0 || c->tile_w > 0) return false;
+    const int64_t cus = c->simds / 4;
+    if (c->pshape[0] < 0) {
+        c->pshape[0] = 0;
+        if ((int64_t)((c->nx + 15) / 16) * ((c->ny + 15) / 16) > cus) {
+            static const int shapes[5][2] = {{3, 6}, {3, 8}, {4, 6}, {4, 8}, {4, 10}};
+            double best = INFINITY;
+            for (const auto& s : shapes) {
+                const int R = s[0], h = s[1];
+                PlateTiles t = plate_tiles(c, R, h);
+                if (t.list.empty() || t.most > kPanelCap) continue;
+                const double tr = R == 3 ? 8.0 + 1.53 * h : 12.3 + 1.73 * h;
+                const double ti = R == 3 ? 5.0 + 0.7 * h : 6.5 + 0.91 * h;
+                const int inner = (int)t.list.size() - t.rim;
+                const double us = plate_launch_us((t.rim + kXcds - 1) / kXcds, (inner + kXcds - 1) / kXcds,
+                                                  (int)std::max<int64_t>(1, cus / kXcds), tr, ti) / h;
+                if (us >= best) continue;
+                best = us;
+                c->pshape[0] = R;
+                c->pshape[1] = h;
+                c->plive = std::move(t.list);
+            }
+        }
+    }
+    if (c->pshape[0] == 0) return false;
+    f->R = c->pshape[0];
+    f->TL = c->pshape[1];
+    f->T = 1;
+    return true;
+}
+
+// Builds the launch plan of a plate's panels for c->plive, once.
+int build_panel_plan(slbm_ctx* c, int R, int h)
+{
+    if (c->pplan_n) return SLBM_OK;
+    const int64_t wgs = (int64_t)c->plive.size();
+    int rc;
+    const void* fns[4] = {reinterpret_cast<const void*>(panel_kernel(true, false, false, R)),
+                          reinterpret_cast<const void*>(panel_kernel(true, false, true, R)),
+                          reinterpret_cast<const void*>(panel_kernel(true, true, false, R)),
+                          reinterpret_cast<const void*>(panel_kernel(true, true, true, R))};
+    for (const void* fn : fns)
+        HIPCHK(c, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPlateLds));
+    const size_t bytes[4] = {(size_t)wgs * kPanelCap * sizeof(int2), (size_t)wgs * kPanelCap * 32 * sizeof(double),
+                             (size_t)wgs * sizeof(int32_t), (size_t)wgs * sizeof(int32_t)};
+    void* p[4] = {};
+    for (int k = 0; k < 4; ++k)
+        if ((rc = dalloc(c, &p[k], bytes[k]))) {
+            for (int j = 0; j < k; ++j) dfree(c, p[j]);
+            return rc;
+        }
+    int2* plan = (int2*)p[0];
+    double* coef = (double*)p[1];
+    c->ptiles = (int32_t*)p[2];
+    int32_t* count = (int32_t*)p[3];
+    HIPCHK(c, hipMemcpyAsync(c->ptiles, c->plive.data(), (size_t)wgs * sizeof(int32_t), hipMemcpyHostToDevice,
+                             c->stream));
+    PanelArgs a;
+    std::memset(&a, 0, sizeof(a));
+    a.code = c->code;
+    a.bnodes = c->bnodes;
+    a.tiles = c->ptiles;
+    a.nx = c->nx;
+    a.ny = c->ny;
+    a.halo = h;
+    a.tiles_x = (c->nx + 63 - 2 * h) / (64 - 2 * h);
+    hipLaunchKernelGGL(k_panel_plan, dim3((unsigned)wgs), dim3(kPanelBlock), 0, c->stream, a, R, plan, coef, count);
+    HIPCHK(c, hipGetLastError());
+    HIPCHK(c, hipStreamSynchronize(c->stream));      // plive is read by the copy
+    c->pplan = plan;
+    c->pplan_coef = coef;
+    c->pplan_n = count;
+    return SLBM_OK;
 }
 
 // Chooses the fused launches of a loop and builds what they need.
 int plan_fuse(slbm_ctx* c, Fuse* f)
 {
+    if (c->masked && plate_shape(c, f)) {
+        const int rc = build_panel_plan(c, f->R, f->TL);
+        if (rc != SLBM_ENOMEM) return rc;
+        (void)hipGetLastError();
+        c->pshape[0] = 0;                // no memory for the plan (68 KiB per workgroup): LDS tiles
+        *f = Fuse();
+    }
     if (panel_shape(c, f)) return SLBM_OK;
     f->T = fused_steps(c);
     f->TL = tile_steps(c);
@@ -1469,6 +1678,8 @@ int solid_lbm_init(const slbm_problem* p, slbm_ctx** out)
     c->normalize = p->normalize_objective ? 1 : 0;
     c->masked = masked;
     c->nb = (int)bn.size();
+    for (const BNode& b : bn) c->bcells.push_back(b.cell);
+    if (masked) c->mask.assign(p->node_mask, p->node_mask + N);
     c->stream = (hipStream_t)p->stream;
     c->E_cur = p->E;
     c->nblk = (N + kBlock - 1) / kBlock;

@@ -30,6 +30,24 @@ namespace slbm {
 // of tiles) / panel: 300^2 2.24 / 1.57, 371^2 2.60 / 1.65, 501 x 333 2.64 /
 // 1.78, 448^2 2.76 / 1.88, 512^2 2.87 / 2.18, 600^2 3.27 / 2.47, 700^2 3.62 /
 // 3.23; 800^2 4.14 / 4.25 (no gain: strips stay).
+//
+// Plates (k_sweep_plate): four more waves run the boundary nodes, one per lane
+// with its record, closure values and relaxation in registers.  In a sweep the
+// bulk waves pull and collide all their nodes as above, the lanes of boundary
+// nodes put the pulled populations into LDS, the boundary waves apply the node
+// map, and those lanes take the result back (two more barriers, only in tiles
+// that have boundary nodes).  The closure values of cut links (primal) and the
+// node's own slots of them (adjoint) stay with the boundary lane; ghost slots
+// in HBM are read at the start and written at the end of a launch.  What the
+// lanes of outside nodes compute is never read: every link between a domain
+// node and an outside node is a cut link.  The handover's LDS writes (a full
+// instruction for the few lanes of a row) make a sweep of a rim tile about
+// twice an inner tile's; the workgroups' order starts the rim tiles first, so
+// that inner tiles fill the time a compute unit has left.  Against LDS tiles,
+// us per primal step: 384 x 231 3.16 -> 2.57, 512 x 308 (E field) 3.65 -> 2.65,
+// 1000 x 600 (E field) 9.95 -> 5.81.  Packing the boundary nodes inside the bulk
+// waves instead (no barriers) took 4.6 at 512 x 308; handing them over before
+// the bulk rows are collided, so that both run at once, the same time.
 constexpr int kPanelWaves = 8;
 constexpr int kPanelBlock = 64 * kPanelWaves;
 
@@ -43,13 +61,33 @@ struct PanelArgs {
     int64_t N;
     double k11, ks, kd, nu, scale;
     int32_t halo, steps, tiles_x;
+    // plates
+    const int32_t* __restrict__ code;
+    const BNode* __restrict__ bnodes;
+    double E0;
+    // launch plan of the shape (k_panel_plan), by workgroup: per slot (cell,
+    // cut | dirichlet << 8 | written << 16) and 32 coefficient planes of
+    // kPanelCap; boundary nodes per workgroup
+    const int2* __restrict__ plan;
+    const double* __restrict__ plan_coef;
+    const int32_t* __restrict__ plan_n;
+    const int32_t* __restrict__ tiles;    // tile of each workgroup
 };
+
+// Boundary nodes that a workgroup takes (plates): kPanelBWaves waves, one node per lane.
+constexpr int kPanelBWaves = 4;
+constexpr int kPanelCap = 64 * kPanelBWaves;
+constexpr int kPlateBlock = 64 * (kPanelWaves + kPanelBWaves);
 
 // Edge rows: 2 parities x waves x 6 populations x 64 columns.
 constexpr int kPanelEdge = 2 * kPanelWaves * 6 * 64;
 
-template <bool EFIELD, bool ADJ, int R>
-__device__ __forceinline__ void panel_tile(const PanelArgs& a, int tile, double* edge)
+__device__ __forceinline__ int panel_slot(int e) { return (e % kPanelBWaves) * 64 + e / kPanelBWaves; }
+
+// The bulk waves of a tile.  MASKED: io holds 8 doubles per boundary slot,
+// cnt the boundary nodes per wave, nbt the tile's.
+template <bool MASKED, bool EFIELD, bool ADJ, int R>
+__device__ __forceinline__ void panel_tile(const PanelArgs& a, int tile, double* edge, double2* io, int* cnt, int nbt)
 {
     constexpr int W = kPanelWaves;
     // planes pulled from the row below (A: none, x - 1, x + 1) and above (B: none, x + 1, x - 1)
@@ -65,12 +103,14 @@ __device__ __forceinline__ void panel_tile(const PanelArgs& a, int tile, double*
     const bool colin = lane >= h && lane < 64 - h && x0 + lane < nx;   // columns this tile writes
     double o[R][8], c0[R], c1[R], rk11[R], rks[R];
     int64_t cell[R];
+    int cd[R], bs[R];
     {
         int y = wrapi(y0 + w * R, ny);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int64_t n = (int64_t)y * nx + x;
             cell[r] = n;
+            cd[r] = MASKED ? ldg(a.code + n) : 0;
 #pragma unroll
             for (int q = 0; q < 8; ++q) o[r][q] = ldg(a.src + q * N + n);
             c0[r] = ldg(a.g + n);
@@ -89,6 +129,24 @@ __device__ __forceinline__ void panel_tile(const PanelArgs& a, int tile, double*
         e[320] = o[0][B2];
     };
     publish(0);
+    uint32_t rowb = 0;                                   // rows with boundary nodes
+    if (MASKED && nbt) {
+        const uint64_t below = __lanemask_lt();
+        int nbw = 0;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const uint64_t b = __ballot(cd[r] > 0);
+            bs[r] = nbw + __popcll(b & below);
+            nbw += __popcll(b);
+            if (b) rowb |= 1u << r;
+        }
+        if (lane == 0) cnt[w] = nbw;
+        __syncthreads();
+        int base = 0;
+        for (int v = 0; v < w; ++v) base += cnt[v];
+#pragma unroll
+        for (int r = 0; r < R; ++r) bs[r] = panel_slot(base + bs[r]);
+    }
 #pragma unroll
     for (int r = 0; r < R; ++r) {
         c0[r] = (ADJ ? a.scale : 0.25) * c0[r];
@@ -103,7 +161,13 @@ __device__ __forceinline__ void panel_tile(const PanelArgs& a, int tile, double*
     for (int s = 1; s <= a.steps; ++s) {
         __syncthreads();
         const int m = h - (a.steps - s);                 // this sweep computes rows [m, RY - m)
-        if (w * R + R <= m || w * R >= RY - m) continue;
+        if (w * R + R <= m || w * R >= RY - m) {
+            if (MASKED && nbt) {
+                __syncthreads();
+                __syncthreads();
+            }
+            continue;
+        }
         const double* eb = edge + (size_t)(((s - 1) & 1) * W + max(w - 1, 0)) * 6 * 64;
         const double* ea = edge + ((size_t)(((s - 1) & 1) * W + min(w + 1, W - 1)) * 6 + 3) * 64;
         const double la[3] = {eb[lane], eb[64 + lm], eb[128 + lp]};
@@ -118,6 +182,12 @@ __device__ __forceinline__ void panel_tile(const PanelArgs& a, int tile, double*
             f[B0] = B[0];
             f[B1] = B[1];
             f[B2] = B[2];
+            if (MASKED && ((rowb >> r) & 1u)) {
+                if (cd[r] > 0) {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) io[q * kPanelCap + bs[r]] = make_double2(f[2 * q], f[2 * q + 1]);
+                }
+            }
             const double k11 = EFIELD ? rk11[r] : a.k11, ks = EFIELD ? rks[r] : a.ks, kd = EFIELD ? rk11[r] : a.kd;
             if (!ADJ) {
                 double d0, d1;
@@ -150,6 +220,31 @@ __device__ __forceinline__ void panel_tile(const PanelArgs& a, int tile, double*
         } else {
             row(0, la, lb);
         }
+        if (MASKED && nbt) {
+            __syncthreads();
+            __syncthreads();
+            // two rows' reads in flight at a time
+#pragma unroll
+            for (int r0 = 0; r0 < R; r0 += 2)
+                if ((rowb >> r0) & 3u) {
+                    double2 t[2][4];
+#pragma unroll
+                    for (int k = 0; k < 2; ++k)
+                        if (r0 + k < R && cd[r0 + k] > 0) {
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) t[k][q] = io[q * kPanelCap + bs[r0 + k]];
+                        }
+#pragma unroll
+                    for (int k = 0; k < 2; ++k)
+                        if (r0 + k < R) {
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) {
+                                o[r0 + k][2 * q] = cd[r0 + k] > 0 ? t[k][q].x : o[r0 + k][2 * q];
+                                o[r0 + k][2 * q + 1] = cd[r0 + k] > 0 ? t[k][q].y : o[r0 + k][2 * q + 1];
+                            }
+                        }
+                }
+        }
         if (s < a.steps) publish(s & 1);
     }
     if (!colin) return;
@@ -157,8 +252,86 @@ __device__ __forceinline__ void panel_tile(const PanelArgs& a, int tile, double*
     for (int r = 0; r < R; ++r) {
         const int ry = w * R + r;
         if (ry < h || ry >= RY - h || y0 + ry >= ny) continue;
+        if (MASKED && cd[r] < 0) continue;
 #pragma unroll
         for (int q = 0; q < 8; ++q) stg(a.dst + q * N + cell[r], o[r][q]);
+    }
+}
+
+
+// The boundary waves of a plate tile: wave b, lane j runs entry 4 j + b of the
+// tile's list, with its record, closure values and relaxation in registers.
+template <bool EFIELD, bool ADJ>
+__device__ __forceinline__ void panel_boundary(const PanelArgs& a, int wg, int b, double2* io, int nbt)
+{
+    const int lane = threadIdx.x & 63, nx = a.nx;
+    const int64_t N = a.N;
+    const int slot = 64 * b + lane;
+    const bool on = kPanelBWaves * lane + b < nbt;
+    const int64_t at = (int64_t)wg * kPanelCap + (on ? slot : 0);   // a workgroup with boundary nodes has slot 0
+    const int2 en = a.plan[at];
+    BNode bn;
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+#pragma unroll
+        for (int j = 0; j < (ADJ ? 3 : 4); ++j)
+            bn.coef[q][j] = ldg(a.plan_coef + ((int64_t)wg * 32 + 4 * q + j) * kPanelCap + (on ? slot : 0));
+    const int64_t cell = en.x;
+    bn.cut = (uint32_t)en.y & 0xffu;
+    bn.dirichlet = ((uint32_t)en.y >> 8) & 0xffu;
+    const bool written = on && (en.y >> 16);
+    double st[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        // primal: the ghost slot of the cut link (inside the box: domain nodes
+        // do not lie on its edge); adjoint: the node's own slot
+        st[q] = ldg(a.src + q * N + (ADJ ? cell : cell - ((bn.cut >> q) & 1u ? cx(q) + cy(q) * nx : 0)));
+        if (!((bn.cut >> q) & 1u)) st[q] = 0.0;
+    }
+    double gg[2] = {ldg(a.g + cell), ldg(a.g + N + cell)};
+    if (ADJ) {
+        gg[0] = a.scale * gg[0];
+        gg[1] = a.scale * gg[1];
+    }
+    const Relax<double> rl = relax_from_E<double>(EFIELD ? ldg(a.E + cell) : a.E0, a.nu, true);
+    __syncthreads();
+    for (int s = 1; s <= a.steps; ++s) {
+        __syncthreads();
+        __syncthreads();
+        if (on) {
+            double f[8];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const double2 v = io[q * kPanelCap + slot];
+                f[2 * q] = v.x;
+                f[2 * q + 1] = v.y;
+            }
+            if (!ADJ) {
+                double fC[8], mb[5];
+#pragma unroll
+                for (int q = 0; q < 8; ++q)
+                    if ((bn.cut >> q) & 1u) f[q] = st[q];
+                node_map<double>(f, gg, rl, &bn, true, fC, st, mb);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) io[q * kPanelCap + slot] = make_double2(fC[2 * q], fC[2 * q + 1]);
+            } else {
+                double out[8];
+#pragma unroll
+                for (int q = 0; q < 8; ++q)              // the populations of outside nodes are zero
+                    if ((bn.cut >> opp(q)) & 1u) f[q] = 0.0;
+                adj_boundary(f, st, &bn, rl, gg[0], gg[1], out);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) io[q * kPanelCap + slot] = make_double2(out[2 * q], out[2 * q + 1]);
+#pragma unroll
+                for (int q = 0; q < 8; ++q) st[q] = ((bn.cut >> q) & 1u) ? out[q] : 0.0;
+            }
+        }
+        __syncthreads();
+    }
+    if (!ADJ && written) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if ((bn.cut >> q) & 1u) stg(a.dst + q * N + cell - (cx(q) + cy(q) * nx), st[q]);
     }
 }
 
@@ -167,7 +340,61 @@ __global__ __launch_bounds__(kPanelBlock) void k_sweep_panel(PanelArgs a)
 {
     if (a.status->stop) return;
     __shared__ __align__(16) double edge[kPanelEdge];
-    panel_tile<EFIELD, ADJ, R>(a, xcd_order(blockIdx.x, gridDim.x), edge);
+    panel_tile<false, EFIELD, ADJ, R>(a, xcd_order(blockIdx.x, gridDim.x), edge, nullptr, nullptr, 0);
+}
+
+template <bool EFIELD, bool ADJ, int R>
+__global__ __launch_bounds__(kPlateBlock) void k_sweep_plate(PanelArgs a)
+{
+    if (a.status->stop) return;
+    extern __shared__ __align__(16) double lds[];        // edge rows, then 8 doubles per boundary slot
+    __shared__ int cnt[kPanelWaves];
+    const int wg = xcd_order(blockIdx.x, gridDim.x);
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int tile = a.tiles[wg];
+    const int nbt = a.plan_n[wg];
+    double2* io = reinterpret_cast<double2*>(lds + kPanelEdge);
+    if (w < kPanelWaves) panel_tile<true, EFIELD, ADJ, R>(a, tile, lds, io, cnt, nbt);
+    else if (nbt) panel_boundary<EFIELD, ADJ>(a, wg, w - kPanelWaves, io, nbt);
+}
+
+// Launch plan of a plate's panels (grid: one workgroup per live tile, in the
+// order of the tile list): the boundary nodes of its region in region order,
+// spread over the boundary waves, with their records in planes, so that a
+// boundary wave loads consecutive words.
+__global__ __launch_bounds__(kPanelBlock) void k_panel_plan(PanelArgs a, int R, int2* plan, double* coef, int32_t* plan_n)
+{
+    const int wg = blockIdx.x, tile = a.tiles[wg], lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int h = a.halo, RY = kPanelWaves * R;
+    const int x0 = (tile % a.tiles_x) * (64 - 2 * h) - h, y0 = (tile / a.tiles_x) * (RY - 2 * h) - h;
+    const int x = wrapi(x0 + lane, a.nx);
+    const bool colin = lane >= h && lane < 64 - h && x0 + lane < a.nx;
+    __shared__ int cnt[kPanelWaves];
+    int mine = 0;
+    for (int r = 0; r < R; ++r) mine += __popcll(__ballot(a.code[(int64_t)wrapi(y0 + w * R + r, a.ny) * a.nx + x] > 0));
+    if (lane == 0) cnt[w] = mine;
+    __syncthreads();
+    int at = 0, total = 0;
+    for (int v = 0; v < kPanelWaves; ++v) {
+        if (v < w) at += cnt[v];
+        total += cnt[v];
+    }
+    for (int r = 0; r < R; ++r) {
+        const int ry = w * R + r;
+        const int64_t n = (int64_t)wrapi(y0 + ry, a.ny) * a.nx + x;
+        const int code = a.code[n];
+        const uint64_t b = __ballot(code > 0);
+        const int e = at + __popcll(b & __lanemask_lt());
+        const bool wr = colin && ry >= h && ry < RY - h && y0 + ry < a.ny;
+        if (code > 0 && e < kPanelCap) {
+            const BNode& bn = a.bnodes[code - 1];
+            const int s = panel_slot(e);
+            plan[(int64_t)wg * kPanelCap + s] = make_int2((int)n, (int)(bn.cut | bn.dirichlet << 8 | (wr ? 1u << 16 : 0u)));
+            for (int k = 0; k < 32; ++k) coef[((int64_t)wg * 32 + k) * kPanelCap + s] = bn.coef[k / 4][k % 4];
+        }
+        at += __popcll(b);
+    }
+    if (threadIdx.x == 0) plan_n[wg] = total;
 }
 
 }  // namespace slbm
