@@ -304,11 +304,15 @@ void launch_sweep(slbm_ctx* c, bool adjoint, const SweepArgs& a, bool check)
 
 // (step, input buffer) of the latest check sweeps of a solve.  The host sees
 // a passing test at most one or two checks after it happened (it reads the
-// device status one chunk behind), so the passing check is among the last
-// few; older entries are dropped, which keeps the record from growing with
+// device status one chunk of up to kKeep / 4 checks behind), so the passing
+// check is among the last ones; older entries are dropped, which keeps the record from growing with
 // the length of the run.
+// Steps between two polls of the device status, at least: a poll is a copy and
+// an event (about 5 us); a loop that has converged runs on for up to two polls
+// of launches that return at once.
+constexpr int64_t kPollSteps = 64;
 struct CheckLog {
-    static constexpr size_t kKeep = 16;
+    static constexpr size_t kKeep = 1024;
     std::deque<std::pair<int64_t, int>> q;
     void add(int64_t s, int buf)
     {
@@ -404,11 +408,17 @@ void launch_fused(slbm_ctx* c, bool adjoint, const SweepArgs& s, int T)
 // several steps' worth, so one round of workgroups beats more steps in two
 // (measured on MI355X: the 512 x 308 plate 5.0 us per primal step with 6
 // steps in 416 tiles, 4.3 with 3 steps in 240; 384 x 231 keeps 6 steps in
-// 240 tiles, 3.0 us).
+// 240 tiles, 3.0 us).  Grids of one 8 x 8 tile per compute unit that check every
+// 9 to 12 steps take the whole interval in one launch, whose first sweep is the
+// check (8 steps and the rest as a second launch: the 64 x 39 plate, K = 10,
+// 2.80 us per step against 2.44; 32 x 32, K = 12, 2.45 against 2.22).
 int tile_halo(const slbm_ctx* c)
 {
     if (c->tb_T >= 0) return std::max(1, std::min(c->tb_T, 8));
-    if (c->N <= 131072) return 8;
+    if (c->N <= 131072) {
+        const int64_t t8 = (int64_t)((c->nx + 7) / 8) * ((c->ny + 7) / 8);
+        return c->tol > 0.0 && c->K > 8 && c->K <= 12 && t8 <= c->simds / 4 ? (int)c->K : 8;
+    }
     const int64_t cus = c->simds / 4;
     for (int h : {6, 5, 4, 3}) {
         const int t = 32 - 2 * h;
@@ -436,7 +446,7 @@ void tile_shape(const slbm_ctx* c, int h, int* tw, int* th)
     }
     *tw = std::max(2, 32 - 2 * h);
     *th = std::max(2, 32 - 2 * h);
-    if (h == 8) {
+    if (h >= 8) {
         const int64_t cus = c->simds / 4;
         for (int t : {8, 12}) {
             const int64_t tiles = (int64_t)((c->nx + t - 1) / t) * ((c->ny + t - 1) / t);
@@ -456,10 +466,14 @@ int tile_lds_limits(slbm_ctx* c)
     if (c->tile_attr) return SLBM_OK;
     const int lmax = (int)tile_lds_bytes(kTileMaxNodes, true);
     // plates: two copies of a region and the staged records exceed the default 64 KiB
-    const void* fns[4] = {reinterpret_cast<const void*>(&k_sweep_tile<true, false, false>),
-                          reinterpret_cast<const void*>(&k_sweep_tile<true, true, false>),
-                          reinterpret_cast<const void*>(&k_sweep_tile<true, false, true>),
-                          reinterpret_cast<const void*>(&k_sweep_tile<true, true, true>)};
+    const void* fns[8] = {reinterpret_cast<const void*>(&k_sweep_tile<true, false, false, false>),
+                          reinterpret_cast<const void*>(&k_sweep_tile<true, true, false, false>),
+                          reinterpret_cast<const void*>(&k_sweep_tile<true, false, true, false>),
+                          reinterpret_cast<const void*>(&k_sweep_tile<true, true, true, false>),
+                          reinterpret_cast<const void*>(&k_sweep_tile<true, false, false, true>),
+                          reinterpret_cast<const void*>(&k_sweep_tile<true, true, false, true>),
+                          reinterpret_cast<const void*>(&k_sweep_tile<true, false, true, true>),
+                          reinterpret_cast<const void*>(&k_sweep_tile<true, true, true, true>)};
     for (const void* fn : fns) HIPCHK(c, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lmax));
     c->tile_attr = true;
     return SLBM_OK;
@@ -548,7 +562,7 @@ int ensure_tile_plan(slbm_ctx* c, int halo)
     return build_tile_plan(c, halo, tw, th, c->masked ? 1 : 0);
 }
 
-void launch_tile(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, int halo)
+void launch_tile(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, int halo, bool check)
 {
     TileArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -571,6 +585,8 @@ void launch_tile(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, int h
     a.halo = halo;
     a.steps = steps;
     a.maxb = kTileMaxB;
+    a.snap = s.snap;
+    a.partial = s.partial;
     tile_shape(c, halo, &a.tw, &a.th);
     a.tiles_x = (c->nx + a.tw - 1) / a.tw;
     const int tiles_y = (c->ny + a.th - 1) / a.th;
@@ -585,8 +601,11 @@ void launch_tile(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, int h
     const size_t lds = tile_lds_bytes((a.tw + 2 * halo) * (a.th + 2 * halo), c->masked);
     dim3 grid((unsigned)(a.tiles_x * tiles_y)), block(kTileBlock);
     int sel = (c->masked ? 4 : 0) | (c->efield_on ? 2 : 0) | (adjoint ? 1 : 0);
-#define TL_CASE(i, M, EF, AD) \
-    case i: hipLaunchKernelGGL((k_sweep_tile<M, EF, AD>), grid, block, lds, c->stream, a); break;
+#define TL_CASE(i, M, EF, AD)                                                                       \
+    case i:                                                                                         \
+        if (check) hipLaunchKernelGGL((k_sweep_tile<M, EF, AD, true>), grid, block, lds, c->stream, a); \
+        else hipLaunchKernelGGL((k_sweep_tile<M, EF, AD, false>), grid, block, lds, c->stream, a);  \
+        break;
     switch (sel) {
         TL_CASE(0, false, false, false)
         TL_CASE(1, false, false, true)
@@ -641,6 +660,7 @@ struct Fuse {
     int T = 1;        // steps per wave-strip launch
     int TL = 1;       // steps per launch of LDS tiles or panels
     int R = 0;        // rows per lane of the panels (0: LDS tiles)
+    int tiles = 0;    // LDS tiles of a planned launch, whose first sweep may be a residual check (0: none)
 };
 
 int panel_tiles(const slbm_ctx* c, int R, int h)
@@ -892,13 +912,21 @@ int plan_fuse(slbm_ctx* c, Fuse* f)
     int rc;
     if (f->TL > 1 && c->masked && (rc = tile_lds_limits(c))) return rc;
     if (f->TL > 1 && (rc = ensure_tile_plan(c, f->TL))) return rc;
+    if (f->TL > 1) {
+        int tw, th;
+        tile_shape(c, f->TL, &tw, &th);
+        const int64_t tiles = (int64_t)((c->nx + tw - 1) / tw) * ((c->ny + th - 1) / th);
+        if (tile_plan_wanted(c, tw, th) && c->plan && c->plan_key[0] == tw && c->plan_key[1] == th &&
+            c->plan_key[2] == f->TL && tiles <= c->pcap)
+            f->tiles = (int)tiles;
+    }
     return SLBM_OK;
 }
 
-void launch_region(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, const Fuse& f)
+void launch_region(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, const Fuse& f, bool check = false)
 {
     if (f.R > 0) launch_panel(c, adjoint, s, steps, f);
-    else launch_tile(c, adjoint, s, steps, f.TL);
+    else launch_tile(c, adjoint, s, steps, f.TL, check);
 }
 
 // ---------------------------------------------------------------- tangent solves
@@ -1115,15 +1143,33 @@ int run_loop(slbm_ctx* c, bool adjoint, int start, int64_t last, bool use_tol, i
     }
     const int T = fuse.T, TL = fuse.TL;
     CheckLog checks;                              // (step, input buffer) of the latest check sweeps
+    const int64_t poll = std::min<int64_t>(K * (CheckLog::kKeep / 4), kPollSteps);
     int last_in = start;
     auto last_report = std::chrono::steady_clock::now();
     while (s <= last && !stopped) {
-        int64_t end = use_tol ? std::min(last, (s / K + 1) * K - 1) : last;
+        // a chunk ends before a check; short intervals are polled several at a time
+        int64_t end = use_tol ? std::min(last, ((s + poll) / K + 1) * K - 1) : last;
         if (!use_tol && end - s > 4096 * T) end = s + 4096 * T - 1;
         while (s <= end) {
             bool check = use_tol && s > 0 && s % K == 0;
             // plain sweeps available for fusing: up to `end`, never the final sweep
             int64_t plain = std::min(end, last - 1) - s + 1;
+            if (use_tol) plain = std::min(plain, (s / K + 1) * K - s);
+            if (check && fuse.tiles > 0 && plain >= 2) {
+                // the check is the first sweep of a fused launch
+                const int k = (int)std::min<int64_t>(plain, TL);
+                a.src = bufs[cur];
+                a.dst = bufs[cur ^ 1];
+                HIPCHK(c, c->lt.before(c->stream, k, s));
+                launch_region(c, adjoint, a, k, fuse, true);
+                HIPCHK(c, c->lt.close(c->stream));
+                hipLaunchKernelGGL(k_residual, dim3(1), dim3(kBlock), 0, c->stream, c->partial, (int64_t)fuse.tiles,
+                                   c->status, c->tol, s, c->cv_window);
+                checks.add(s, cur);
+                cur ^= 1;
+                s += k;
+                continue;
+            }
             if (!check && T > 1 && plain >= T) {
                 a.src = bufs[cur];
                 a.dst = bufs[cur ^ 1];
@@ -1197,6 +1243,15 @@ int run_loop(slbm_ctx* c, bool adjoint, int start, int64_t last, bool use_tol, i
         const int xin = checks.find(st.t_conv);
         if (xin < 0) return fail(c, SLBM_EHIP, "internal: converged step without a check sweep");
         if (x_out) *x_out = xin;
+        if (fuse.tiles > 0) {
+            // the check was the first sweep of a fused launch, which left a later
+            // state in the other buffer: make the check's own sweep again
+            hipLaunchKernelGGL(k_status_reset, dim3(1), dim3(1), 0, c->stream, c->status);
+            a.src = bufs[xin];
+            a.dst = bufs[xin ^ 1];
+            launch_sweep(c, adjoint, a, false);
+            HIPCHK(c, hipGetLastError());
+        }
     } else {
         *t_out = last;
         *conv_out = false;

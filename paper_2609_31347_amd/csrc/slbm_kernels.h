@@ -1053,6 +1053,10 @@ struct TileArgs {
     const int4* plan;
     const int32_t* plan_rec;
     const int32_t* plan_nst;
+    // launches whose first sweep is a residual check: d(t - K) and the sums of
+    // |d(t) - d(t - K)|^2 and |d(t)|^2, 2 doubles per tile
+    double* snap;
+    double* partial;
 };
 
 constexpr int kTileBlock = 1024;
@@ -1123,10 +1127,37 @@ __device__ __forceinline__ void tile_order(const TileArgs& a, int x0, int y0, in
     for (int j = 0; j < kTileNPT; ++j) ni[j] = order[threadIdx.x + j * kTileBlock];
 }
 
+// Sums (a, b) over a workgroup's kTileBlock threads into out[0], out[1] (thread 0 writes).
+__device__ __forceinline__ void block_sum2_tile(double a, double b, double* out)
+{
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        a += __shfl_xor(a, o);
+        b += __shfl_xor(b, o);
+    }
+    __shared__ double pa[kTileBlock / 64], pb[kTileBlock / 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    if (lane == 0) { pa[w] = a; pb[w] = b; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double x = 0.0, y = 0.0;
+#pragma unroll
+        for (int i = 0; i < kTileBlock / 64; ++i) { x += pa[i]; y += pb[i]; }
+        out[0] = x;
+        out[1] = y;
+    }
+}
+
 // One tile (index `tile` of the problem's tiles_x x tiles_y) of a tiled launch;
 // lds: the region's 8 planes (two copies for plates), then the staged
-// boundary records.  PLAN: the launch has a plan (a.plan non-null).
-template <bool MASKED, bool EFIELD, bool ADJ, bool PLAN = false>
+// boundary records.  PLAN: the launch has a plan (a.plan non-null).  CHECK: the
+// first sweep is a residual check (the sums of k_primal / k_adjoint's check
+// sweeps, over the tile's own nodes); on grids this small a check as a
+// launch of its own, the single step that then stays over and a status copy per
+// check took half the time of a solve that checks every 10 steps (64 x 39
+// plate, 4000 + 4000 steps: 26.4 ms, 19.5 with the checks in fused launches and
+// a poll every 64 steps).
+template <bool MASKED, bool EFIELD, bool ADJ, bool PLAN = false, bool CHECK = false>
 __device__ __forceinline__ void tile_body(const TileArgs& a, int tile, double* lds)
 {
     const int h = a.halo, RX = a.tw + 2 * h, RY = a.th + 2 * h, R = RX * RY;
@@ -1271,9 +1302,21 @@ __device__ __forceinline__ void tile_body(const TileArgs& a, int tile, double* l
             if (w < nwords) lw[w] = rw[p];
         }
     }
+    double s0[CHECK ? kTileNPT : 1], s1[CHECK ? kTileNPT : 1];
+    bool own[CHECK ? kTileNPT : 1];                  // nodes of the tile proper
+    if (CHECK) {
+#pragma unroll
+        for (int j = 0; j < kTileNPT; ++j) {
+            own[j] = ni[j] < R && cd[j] >= 0 && rx[j] >= h && rx[j] < RX - h && ry[j] >= h && ry[j] < RY - h &&
+                     x0 + rx[j] < nx && y0 + ry[j] < ny;
+            s0[j] = own[j] ? ldg(a.snap + gn[j]) : 0.0;
+            s1[j] = own[j] ? ldg(a.snap + N + gn[j]) : 0.0;
+        }
+    }
     __syncthreads();
     for (int s = 1; s <= a.steps; ++s) {
         const bool last = s == a.steps;
+        double num = 0.0, den = 0.0;
         const double* cur = MASKED ? lds + ((s - 1) & 1) * 8 * R : lds;   // written by sweep s - 1
         double* nxt = MASKED ? lds + (s & 1) * 8 * R : lds;
         const int m = h - (a.steps - s);             // this sweep computes [m, RX - m) x [m, RY - m)
@@ -1294,16 +1337,22 @@ __device__ __forceinline__ void tile_body(const TileArgs& a, int tile, double* l
                 const int off = cx(q) + cy(q) * RX;
                 f[q] = cur[q * R + (ADJ ? i + off : i - off)];
             }
+            double d0 = 0.0, d1 = 0.0;
+            if (CHECK && ADJ) {
+                d0 = (f[0] - f[2]) + (f[4] - f[5]) + (f[7] - f[6]);
+                d1 = (f[1] - f[3]) + (f[4] + f[5]) - (f[6] + f[7]);
+            }
             if (!ADJ) {
                 if (!MASKED || code == 0) {
-                    double d0, d1;
                     collide_bulk(f, 0.25 * c0[j], 0.25 * c1[j], rl[j].k11, rl[j].ks, rl[j].kd, d0, d1);
 #pragma unroll
                     for (int q = 0; q < 8; ++q) out[j][q] = f[q];
                 } else {
-                    auto bnode = [&](const BNode* bn, auto sparse) {
+                    auto bnode = [&](const BNode* bn) {
                         double gg[2] = {c0[j], c1[j]}, fC[8], hv[8], mb[5];
-                        node_map<double, decltype(sparse)::value>(f, gg, rl[j], bn, true, fC, hv, mb);
+                        node_map<double>(f, gg, rl[j], bn, true, fC, hv, mb);
+                        d0 = mb[0];
+                        d1 = mb[1];
                         const uint32_t cut = bn->cut;
                         int64_t idx[8];
                         // the last sweep covers nodes of the grid proper only (no wrap)
@@ -1317,8 +1366,8 @@ __device__ __forceinline__ void tile_body(const TileArgs& a, int tile, double* l
                             }
                         }
                     };
-                    if (bsl[j] >= 0) bnode(lbn + bsl[j], std::true_type());
-                    else bnode(bng[j], std::false_type());
+                    if (bsl[j] >= 0) bnode(lbn + bsl[j]);
+                    else bnode(bng[j]);
                 }
             } else {
                 const double srx = c0[j], sry = c1[j];
@@ -1327,22 +1376,29 @@ __device__ __forceinline__ void tile_body(const TileArgs& a, int tile, double* l
 #pragma unroll
                     for (int q = 0; q < 8; ++q) out[j][q] = f[q];
                 } else {
-                    auto bnode = [&](const BNode* bn, auto sparse) {
+                    auto bnode = [&](const BNode* bn) {
                         const uint32_t cut = bn->cut;
                         double yh[8];
 #pragma unroll
                         for (int q = 0; q < 8; ++q) yh[q] = ((cut >> q) & 1u) ? cur[q * R + i] : 0.0;
-                        adj_boundary<decltype(sparse)::value>(f, yh, bn, rl[j], srx, sry, out[j]);
+                        adj_boundary(f, yh, bn, rl[j], srx, sry, out[j]);
                     };
-                    if (bsl[j] >= 0) bnode(lbn + bsl[j], std::true_type());
-                    else bnode(bng[j], std::false_type());
+                    if (bsl[j] >= 0) bnode(lbn + bsl[j]);
+                    else bnode(bng[j]);
                 }
+            }
+            if (CHECK && s == 1 && own[j]) {
+                num += (d0 - s0[j]) * (d0 - s0[j]) + (d1 - s1[j]) * (d1 - s1[j]);
+                den += d0 * d0 + d1 * d1;
+                stg(a.snap + n, d0);
+                stg(a.snap + N + n, d1);
             }
             if (last) {
 #pragma unroll
                 for (int q = 0; q < 8; ++q) stg(a.dst + q * N + n, out[j][q]);
             }
         }
+        if (CHECK && s == 1) block_sum2_tile(num, den, a.partial + 2 * (int64_t)tile);
         if (last) break;
         if (!MASKED) __syncthreads();               // in place: every pull read before the writes
 #pragma unroll
@@ -1358,12 +1414,13 @@ __device__ __forceinline__ void tile_body(const TileArgs& a, int tile, double* l
 
 // Tiles in row-major order, handed out XCD by XCD (xcd_order): neighbouring
 // tiles, whose regions overlap by the halo, load them on the same L2.
-template <bool MASKED, bool EFIELD, bool ADJ>
+template <bool MASKED, bool EFIELD, bool ADJ, bool CHECK>
 __global__ __launch_bounds__(kTileBlock) void k_sweep_tile(TileArgs a)
 {
     if (a.status->stop) return;
     extern __shared__ __align__(16) double lds[];    // 8 planes of RX * RY doubles (2 copies for plates), then staged records
-    if (a.plan) tile_body<MASKED, EFIELD, ADJ, true>(a, xcd_order(blockIdx.x, gridDim.x), lds);
+    if (CHECK) tile_body<MASKED, EFIELD, ADJ, true, true>(a, xcd_order(blockIdx.x, gridDim.x), lds);
+    else if (a.plan) tile_body<MASKED, EFIELD, ADJ, true>(a, xcd_order(blockIdx.x, gridDim.x), lds);
     else tile_body<MASKED, EFIELD, ADJ, false>(a, xcd_order(blockIdx.x, gridDim.x), lds);
 }
 
@@ -1660,27 +1717,6 @@ struct PersistCtl {
     uint32_t grp[kXcds][32];  // grid barrier: workgroups arrived per group (one 128-byte line each)
 };
 
-// Sums (a, b) over the kPersistBlock threads into out[0], out[1] (thread 0 writes).
-__device__ __forceinline__ void block_sum2_persist(double a, double b, double* out)
-{
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        a += __shfl_xor(a, o);
-        b += __shfl_xor(b, o);
-    }
-    __shared__ double pa[kPersistBlock / 64], pb[kPersistBlock / 64];
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    if (lane == 0) { pa[w] = a; pb[w] = b; }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        double x = 0.0, y = 0.0;
-#pragma unroll
-        for (int i = 0; i < kPersistBlock / 64; ++i) { x += pa[i]; y += pb[i]; }
-        out[0] = x;
-        out[1] = y;
-    }
-}
-
 // Grid barrier over nwg workgroups with device-scope release/acquire; false
 // if it timed out or another workgroup reported an error.  Two levels: the
 // workgroups of a group (those of one XCD: workgroup b runs on XCD b % 8)
@@ -1815,7 +1851,7 @@ __device__ __forceinline__ void persist_nodes(const BatchInst& I, int par, int b
         }
 #undef BN_CASE
     }
-    if (check) block_sum2_persist(num, den, a.partial + 2 * (int64_t)blk);
+    if (check) block_sum2_tile(num, den, a.partial + 2 * (int64_t)blk);
 }
 
 // Residual test of an instance after its check step t: the sum of its nnb
@@ -1829,7 +1865,7 @@ __device__ __forceinline__ void persist_resid(const BatchInst& I, const PersistI
         b += partial[2 * k + 1];
     }
     __shared__ double out[2];
-    block_sum2_persist(a, b, out);
+    block_sum2_tile(a, b, out);
     if (threadIdx.x == 0) {
         Status* st = I.status;
         const double num = out[0], den = out[1];
