@@ -2214,7 +2214,7 @@ struct slbm_batch {
     std::vector<slbm_ctx*> ctx;
     hipStream_t stream = nullptr;
     Status* status = nullptr;      // one Status per instance, contiguous
-    Status* h_status = nullptr;    // pinned, 2 slots of B
+    Status* h_status = nullptr;    // pinned, 2 slots of B per class
     BatchInst* d_inst = nullptr;
     std::vector<BatchInst> h_inst;
     int2* d_all = nullptr;         // every instance: (instance, block) of a single-step sweep,
@@ -2233,7 +2233,9 @@ struct slbm_batch {
     bool any_masked = false, tile_attr = false;
     double tol = 0.0;
     int64_t max_steps = 0;
-    hipEvent_t ev[2] = {nullptr, nullptr}, t0 = nullptr, t1 = nullptr;
+    hipEvent_t ev[4] = {}, t0 = nullptr, t1 = nullptr;   // polls: two slots per class
+    std::vector<int64_t> seen_t;   // step and residual of each instance's latest check read back
+    std::vector<double> seen_res;
     // persistent launches (solid_lbm_batch_set_persistent): one graph-captured
     // persistent kernel per launch instead of host-driven launches per round
     bool persist = false;
@@ -2243,7 +2245,8 @@ struct slbm_batch {
     int64_t pstate_cap = 0;             // replicas allocated (workgroups x instances)
     PersistCtl* d_pctl = nullptr;
     PersistCtl* h_pctl = nullptr;  // pinned: the graph copies the control block here
-    hipStream_t pstream = nullptr; // capture stream (the batch's stream may be the default one)
+    hipStream_t pstream = nullptr; // capture stream (the batch's stream may be the default one); the
+                                   // tiled class of host-driven launches
     hipEvent_t pev = nullptr;
     bool persist_attr = false;
     int64_t persist_launches = 0, persist_rounds_run = 0;   // of the last persistent half
@@ -2298,8 +2301,27 @@ void batch_shape(slbm_batch* b, int* T, int* H, int* Tt)
         for (size_t i = 0; i < b->ctx.size(); ++i)
             if (!b->tiled[i]) maxny = std::max(maxny, b->ctx[i]->ny);
         h = maxny <= 1536 ? 24 : 48;
+        // fewer rows while one wave per SIMD covers all strips: a wave's time goes
+        // with h + 2 T rows (9 instances of 64^2 to 384^2: 41 us per 8 steps with
+        // 24 rows, 33 with the 8 .. 16 that fit); batches that fill the SIMDs
+        // keep 24 (72 periodic instances of 8 M cells: 121 GLUPS with 96 rows)
+        for (int r : {8, 12, 16}) {
+            int64_t waves = 0;
+            int simds = 0;
+            for (size_t i = 0; i < b->ctx.size(); ++i) {
+                const slbm_ctx* c = b->ctx[i];
+                if (b->tiled[i]) continue;
+                simds = c->simds;
+                waves += (int64_t)((c->nx + 63 - 2 * t) / (64 - 2 * t)) * ((c->ny + r - 1) / r);
+            }
+            if (waves <= simds) {
+                h = r;
+                break;
+            }
+        }
+    } else if (t > 1 && h < 2 * t) {
+        h = 2 * t;
     }
-    if (t > 1 && h < 2 * t) h = 2 * t;
     *T = t;
     *H = h;
 }
@@ -2504,27 +2526,36 @@ int batch_tables(slbm_batch* b, bool adjoint)
     return SLBM_OK;
 }
 
-void launch_batch_step(slbm_batch* b, bool adjoint, const int2* table, int64_t nblocks, int pp, int pl,
-                       uint64_t lo, uint64_t hi)
+void batch_set(uint64_t (&m)[2], int i, bool on = true)
 {
-    if (nblocks <= 0) return;
-    if (adjoint)
-        hipLaunchKernelGGL(k_sweep_batch<true>, dim3((unsigned)nblocks), dim3(kBlock), 0, b->stream, b->d_inst,
-                           table, pp, pl, lo, hi);
-    else
-        hipLaunchKernelGGL(k_sweep_batch<false>, dim3((unsigned)nblocks), dim3(kBlock), 0, b->stream, b->d_inst,
-                           table, pp, pl, lo, hi);
+    if (on) m[i >> 6] |= 1ull << (i & 63);
 }
 
-void launch_batch_fused(slbm_batch* b, bool adjoint, int pp)
+// one step of the selected instances of a class, `checks` of them with their
+// residual sums; the class's blocks are the table entries [first, first + n)
+void launch_batch_step(slbm_batch* b, bool adjoint, bool tiled, hipStream_t stream, const BatchSel& sel,
+                       const BatchSel& checks)
+{
+    const int64_t first = tiled ? b->n_all_strip : 0, n = tiled ? b->n_all - b->n_all_strip : b->n_all_strip;
+    if (n <= 0) return;
+    if (adjoint)
+        hipLaunchKernelGGL(k_sweep_batch<true>, dim3((unsigned)n), dim3(kBlock), 0, stream, b->d_inst,
+                           b->d_all + first, sel, checks);
+    else
+        hipLaunchKernelGGL(k_sweep_batch<false>, dim3((unsigned)n), dim3(kBlock), 0, stream, b->d_inst,
+                           b->d_all + first, sel, checks);
+}
+
+// T steps of the selected wave-strip instances
+void launch_batch_fused(slbm_batch* b, bool adjoint, hipStream_t stream, const BatchSel& sel)
 {
     dim3 grid((unsigned)b->n_tb), block(64);
-#define BTB_CASE(TT)                                                                                       \
-    case TT:                                                                                               \
-        if (adjoint) hipLaunchKernelGGL((k_sweep_tb_batch<TT, true>), grid, block, 0, b->stream, b->d_inst, \
-                                        b->cur_tb, pp);                                                    \
-        else hipLaunchKernelGGL((k_sweep_tb_batch<TT, false>), grid, block, 0, b->stream, b->d_inst,       \
-                                b->cur_tb, pp);                                                            \
+#define BTB_CASE(TT)                                                                                     \
+    case TT:                                                                                             \
+        if (adjoint) hipLaunchKernelGGL((k_sweep_tb_batch<TT, true>), grid, block, 0, stream, b->d_inst, \
+                                        b->cur_tb, sel);                                                 \
+        else hipLaunchKernelGGL((k_sweep_tb_batch<TT, false>), grid, block, 0, stream, b->d_inst,        \
+                                b->cur_tb, sel);                                                         \
         break;
     switch (b->T) {
         BTB_CASE(2)
@@ -2535,17 +2566,17 @@ void launch_batch_fused(slbm_batch* b, bool adjoint, int pp)
 #undef BTB_CASE
 }
 
-// steps (1 .. Tt) sweeps of every tiled instance
-void launch_batch_tile(slbm_batch* b, bool adjoint, int pl, int steps)
+// steps.n (1 .. Tt) sweeps of the selected tiled instances
+void launch_batch_tile(slbm_batch* b, bool adjoint, hipStream_t stream, const BatchSel& sel, const BatchSteps& steps)
 {
     if (b->n_tile <= 0) return;
     const int w = std::max(2, 32 - 2 * b->Tt) + 2 * b->Tt;
     const size_t lds = tile_lds_bytes(w * w, b->any_masked);
     dim3 grid((unsigned)b->n_tile), block(kTileBlock);
     if (adjoint)
-        hipLaunchKernelGGL(k_sweep_tile_batch<true>, grid, block, lds, b->stream, b->d_inst, b->cur_tile, pl, steps);
+        hipLaunchKernelGGL(k_sweep_tile_batch<true>, grid, block, lds, stream, b->d_inst, b->cur_tile, sel, steps);
     else
-        hipLaunchKernelGGL(k_sweep_tile_batch<false>, grid, block, lds, b->stream, b->d_inst, b->cur_tile, pl, steps);
+        hipLaunchKernelGGL(k_sweep_tile_batch<false>, grid, block, lds, stream, b->d_inst, b->cur_tile, sel, steps);
 }
 
 // run plain steps (no checks) of every instance: the wave-strip class in
@@ -2553,39 +2584,178 @@ void launch_batch_tile(slbm_batch* b, bool adjoint, int pl, int steps)
 // in launches of up to Tt steps; each class flips its buffer parity per launch.
 void batch_plain_steps(slbm_batch* b, bool adjoint, int64_t run, int& pp, int& pl)
 {
-    const bool strips = b->n_all_strip > 0;
-    if (strips) {
+    BatchSel all, none;
+    std::memset(&all, 0, sizeof(all));
+    std::memset(&none, 0, sizeof(none));
+    for (int i = 0; i < (int)b->ctx.size(); ++i) batch_set(all.act, i);
+    auto at = [&](int par) {
+        BatchSel s = all;
+        for (uint64_t& m : s.par) m = par ? ~0ull : 0ull;
+        return s;
+    };
+    if (b->n_all_strip > 0) {
         int64_t left = run;
         if (b->T > 1 && b->n_tb > 0)
             for (; left >= b->T; left -= b->T) {
-                launch_batch_fused(b, adjoint, pp);
+                launch_batch_fused(b, adjoint, b->stream, at(pp));
                 pp ^= 1;
             }
         for (; left > 0; --left) {
-            launch_batch_step(b, adjoint, b->d_all, b->n_all_strip, pp, pl, 0, 0);
+            launch_batch_step(b, adjoint, false, b->stream, at(pp), none);
             pp ^= 1;
         }
     }
     if (b->n_all > b->n_all_strip) {
         if (b->Tt > 1 && b->n_tile > 0) {
             for (int64_t left = run; left > 0; left -= b->Tt) {
-                launch_batch_tile(b, adjoint, pl, (int)std::min<int64_t>(left, b->Tt));
+                BatchSteps n;
+                std::memset(n.n, (int)std::min<int64_t>(left, b->Tt), sizeof(n.n));
+                launch_batch_tile(b, adjoint, b->stream, at(pl), n);
                 pl ^= 1;
             }
         } else {
             for (int64_t j = 0; j < run; ++j) {
-                launch_batch_step(b, adjoint, b->d_all + b->n_all_strip, b->n_all - b->n_all_strip, pp, pl, 0, 0);
+                launch_batch_step(b, adjoint, true, b->stream, at(pl), none);
                 pl ^= 1;
             }
         }
     }
 }
 
-// Advances every instance from buffer 0 in lock-step (step index s), each
-// with its own residual checks every K_i steps and its own stop flag; plain
-// runs between checks are fused (wave strips T steps per launch, tiles Tt).
-// Afterwards, for each instance: t (its final step), X (buffer holding its
-// input of step t) and whether it converged.
+// The solve loop of one class of a batch's instances (wave strips or tiles).
+// Every instance keeps its own step counter, buffer and check schedule; a round
+// is one fused launch of the instances that have a fused launch's worth of
+// plain steps before their next check, then one single-step launch of those
+// that are at a check, at their last step or short of one, then the residual
+// tests.  (All instances in lock-step stopped fusing at every check of any of
+// them: 12 instances with 12 check intervals, 1500 steps, took 765 single-step
+// launches of everything per half and 24.7 ms, half of it in those.)  The two
+// classes run on two streams: they share nothing, and the tiles' latency-bound
+// launches fit beside the strips'.
+struct BatchClass {
+    slbm_batch* b;
+    bool adjoint, tiled, use_tol;
+    hipStream_t stream;
+    std::vector<int> ids;
+    std::vector<int64_t>& s;          // by instance: next step,
+    std::vector<int>& cur;            // buffer of its input,
+    std::vector<char>& active;        // still running,
+    std::vector<CheckLog>& checks;    // its latest checks and
+    std::vector<int>& last_in;        // the buffer of its last step's input
+    static constexpr int kPollRounds = 4;
+    int since_poll = 0;
+    bool checked = false;             // a check since the last poll
+    std::deque<int> pending;          // status slots copied and not yet read
+    int slot = 0;
+
+    int64_t plain(int i) const
+    {
+        const int64_t K = b->ctx[i]->K, last = b->max_steps;
+        if (use_tol && s[i] > 0 && s[i] % K == 0) return 0;
+        const int64_t end = use_tol ? std::min(last, (s[i] / K + 1) * K - 1) : last;
+        return std::min(end, last - 1) - s[i] + 1;
+    }
+    bool running(int i) const { return active[i] && s[i] <= b->max_steps; }
+    bool work() const
+    {
+        for (int i : ids)
+            if (running(i)) return true;
+        return false;
+    }
+    // slots of this class in the pinned copies and the events
+    Status* host(int k) const { return b->h_status + (size_t)(2 * (tiled ? 1 : 0) + k) * b->ctx.size(); }
+    hipEvent_t event(int k) const { return b->ev[2 * (tiled ? 1 : 0) + k]; }
+
+    int round()
+    {
+        const int fuse = tiled ? b->Tt : b->T;
+        BatchSel sel, chk;
+        BatchSteps steps;
+        std::memset(&sel, 0, sizeof(sel));
+        bool any = false;
+        if (fuse > 1)
+            for (int i : ids) {
+                if (!running(i)) continue;
+                const int64_t p = plain(i);
+                if (p < (tiled ? 1 : fuse)) continue;
+                const int k = (int)std::min<int64_t>(p, fuse);
+                batch_set(sel.act, i);
+                batch_set(sel.par, i, cur[i] != 0);
+                steps.n[i] = (uint8_t)k;
+                s[i] += k;
+                cur[i] ^= 1;
+                any = true;
+            }
+        if (any) {
+            if (tiled) launch_batch_tile(b, adjoint, stream, sel, steps);
+            else launch_batch_fused(b, adjoint, stream, sel);
+        }
+        std::memset(&sel, 0, sizeof(sel));
+        std::memset(&chk, 0, sizeof(chk));
+        BatchTimes times;
+        any = false;
+        bool tests = false;
+        for (int i : ids) {
+            if (!running(i)) continue;
+            if (fuse > 1 && plain(i) >= (tiled ? 1 : fuse)) continue;
+            batch_set(sel.act, i);
+            batch_set(sel.par, i, cur[i] != 0);
+            if (use_tol && s[i] > 0 && s[i] % b->ctx[i]->K == 0) {
+                batch_set(chk.act, i);
+                times.t[i] = s[i];
+                checks[i].add(s[i], cur[i]);
+                tests = true;
+            }
+            if (s[i] == b->max_steps) last_in[i] = cur[i];
+            ++s[i];
+            cur[i] ^= 1;
+            any = true;
+        }
+        if (any) launch_batch_step(b, adjoint, tiled, stream, sel, chk);
+        if (tests)
+            hipLaunchKernelGGL(k_residual_batch, dim3((unsigned)b->ctx.size()), dim3(kBlock), 0, stream, b->d_inst,
+                               adjoint ? 1 : 0, chk, b->tol, times);
+        BHIPCHK(b, hipGetLastError());
+        checked = checked || tests;
+        ++since_poll;
+        if (!checked || since_poll < kPollRounds) return SLBM_OK;
+        const size_t B = b->ctx.size();
+        BHIPCHK(b, hipMemcpyAsync(host(slot), b->status, B * sizeof(Status), hipMemcpyDeviceToHost, stream));
+        BHIPCHK(b, hipEventRecord(event(slot), stream));
+        pending.push_back(slot);
+        slot ^= 1;
+        since_poll = 0;
+        checked = false;
+        return SLBM_OK;
+    }
+    // reads the oldest pending poll (wait: block until it is there); false if none was read
+    int read(bool wait, bool* got)
+    {
+        *got = false;
+        if (pending.empty()) return SLBM_OK;
+        const int k = pending.front();
+        if (wait) {
+            BHIPCHK(b, hipEventSynchronize(event(k)));
+        } else {
+            const hipError_t e = hipEventQuery(event(k));
+            if (e == hipErrorNotReady) return SLBM_OK;
+            BHIPCHK(b, e);
+        }
+        pending.pop_front();
+        *got = true;
+        for (int i : ids) {
+            const Status& h = host(k)[i];
+            if (h.stop) active[i] = 0;
+            b->seen_t[i] = h.t_last;
+            b->seen_res[i] = h.res;
+        }
+        return SLBM_OK;
+    }
+};
+
+// Advances every instance from buffer 0, each with its own residual checks
+// every K_i steps and its own stop flag.  Afterwards, for each instance: t (its
+// final step), X (buffer holding its input of step t) and whether it converged.
 int batch_loop_persist(slbm_batch* b, bool adjoint, std::vector<int64_t>& t_out, std::vector<int>& x_out,
                        std::vector<char>& conv, std::vector<double>& res, double* dev_ms);
 
@@ -2600,72 +2770,61 @@ int batch_loop(slbm_batch* b, bool adjoint, std::vector<int64_t>& t_out, std::ve
     if (rc) return rc;
     const int64_t last = b->max_steps;
     const bool use_tol = b->tol > 0.0;
-    std::vector<int64_t> K(B);
-    for (int i = 0; i < B; ++i) K[i] = b->ctx[i]->K;
     std::vector<char> active(B, 1);
     std::vector<CheckLog> checks(B);
-    std::vector<int> last_in(B, 0);
-    int pp = 0, pl = 0, slot = 0, polls = 0;
-    int64_t s = 0, slot_step[2] = {0, 0};   // the step of the check each status slot holds
+    std::vector<int> last_in(B, 0), cur(B, 0);
+    std::vector<int64_t> next(B, 0);
+    b->seen_t.assign(B, -1);
+    b->seen_res.assign(B, 0.0);
+    std::vector<BatchClass> cls;
+    for (int k = 0; k < 2; ++k) {
+        BatchClass c{b, adjoint, k == 1, use_tol, k == 1 ? b->pstream : b->stream, {}, next, cur, active, checks, last_in};
+        for (int i = 0; i < B; ++i)
+            if ((b->tiled[i] != 0) == (k == 1)) c.ids.push_back(i);
+        if (!c.ids.empty()) cls.push_back(c);
+    }
+    if (cls.size() == 1) cls[0].stream = b->stream;
     auto last_report = std::chrono::steady_clock::now();
+    int64_t reported = -1;
     BHIPCHK(b, hipEventRecord(b->t0, b->stream));
-    auto any_active = [&]() {
-        for (char a : active)
-            if (a) return true;
-        return false;
-    };
-    while (s <= last && any_active()) {
-        uint64_t lo = 0, hi = 0;
-        if (use_tol && s > 0)
-            for (int i = 0; i < B; ++i)
-                if (active[i] && s % K[i] == 0) (i < 64 ? lo : hi) |= 1ull << (i & 63);
-        if (lo || hi || s == last) {
-            launch_batch_step(b, adjoint, b->d_all, b->n_all, pp, pl, lo, hi);
-            for (int i = 0; i < B; ++i) {
-                int par = b->tiled[i] ? pl : pp;
-                if ((i < 64 ? (lo >> i) : (hi >> (i - 64))) & 1ull) checks[i].add(s, par);
-                if (s == last) last_in[i] = par;
-            }
-            if (lo || hi) {
-                hipLaunchKernelGGL(k_residual_batch, dim3(B), dim3(kBlock), 0, b->stream, b->d_inst,
-                                   adjoint ? 1 : 0, lo, hi, b->tol, s);
-                BHIPCHK(b, hipMemcpyAsync(b->h_status + slot * B, b->status, B * sizeof(Status),
-                                          hipMemcpyDeviceToHost, b->stream));
-                BHIPCHK(b, hipEventRecord(b->ev[slot], b->stream));
-                slot_step[slot] = s;
-                if (polls >= 1) {
-                    BHIPCHK(b, hipEventSynchronize(b->ev[slot ^ 1]));
-                    double worst = -1.0;   // of the running instances with a completed check
-                    for (int i = 0; i < B; ++i) {
-                        const Status& h = b->h_status[(slot ^ 1) * B + i];
-                        if (h.stop) active[i] = 0;
-                        else if (active[i] && h.t_last >= 0) worst = std::max(worst, h.res);
-                    }
-                    if (b->progress && worst >= 0.0) {
-                        auto now = std::chrono::steady_clock::now();
-                        if (std::chrono::duration<double>(now - last_report).count() >= b->progress_every) {
-                            last_report = now;
-                            b->progress(b->progress_user, adjoint ? 1 : 0, slot_step[slot ^ 1], worst);
-                        }
-                    }
-                }
-                ++polls;
-                slot ^= 1;
-            }
-            pp ^= 1;
-            pl ^= 1;
-            ++s;
-            continue;
+    if (cls.size() == 2) BHIPCHK(b, hipStreamWaitEvent(b->pstream, b->t0, 0));
+    for (;;) {
+        bool any = false, moved = false, got = false;
+        for (BatchClass& c : cls) {
+            // at most two polls behind: the queue never runs dry, and a stop is seen soon
+            if ((rc = c.read(false, &got))) return rc;
+            if (!c.work()) continue;
+            any = true;
+            if (c.pending.size() >= 2) continue;
+            if ((rc = c.round())) return rc;
+            moved = true;
         }
-        // plain steps until the next check of an active instance (or the final step)
-        int64_t next = last;
-        if (use_tol)
-            for (int i = 0; i < B; ++i)
-                if (active[i]) next = std::min(next, (s / K[i] + 1) * K[i]);
-        const int64_t run = next - s;
-        batch_plain_steps(b, adjoint, run, pp, pl);
-        s += run;
-        BHIPCHK(b, hipGetLastError());
+        if (!any) break;
+        if (!moved)
+            for (BatchClass& c : cls)
+                if (c.work()) {
+                    if ((rc = c.read(true, &got))) return rc;
+                    break;
+                }
+        if (got && b->progress) {
+            double worst = -1.0;       // of the running instances with a completed check
+            int64_t t = -1;
+            for (int i = 0; i < B; ++i) {
+                if (active[i] && b->seen_t[i] >= 0) worst = std::max(worst, b->seen_res[i]);
+                t = std::max(t, b->seen_t[i]);
+            }
+            auto now = std::chrono::steady_clock::now();
+            if (worst >= 0.0 && t >= reported &&
+                std::chrono::duration<double>(now - last_report).count() >= b->progress_every) {
+                last_report = now;
+                reported = t;
+                b->progress(b->progress_user, adjoint ? 1 : 0, t, worst);
+            }
+        }
+    }
+    if (cls.size() == 2) {
+        BHIPCHK(b, hipEventRecord(b->pev, b->pstream));
+        BHIPCHK(b, hipStreamWaitEvent(b->stream, b->pev, 0));
     }
     BHIPCHK(b, hipEventRecord(b->t1, b->stream));
     BHIPCHK(b, hipStreamSynchronize(b->stream));
@@ -2992,10 +3151,11 @@ int solid_lbm_batch_init(const slbm_problem* problems, int32_t count, slbm_batch
     if (!rc && !(rc = balloc(b, &q, all.size() * sizeof(int2)))) b->d_all = (int2*)q;
     if (!rc && hipMemcpy(b->d_all, all.data(), all.size() * sizeof(int2), hipMemcpyHostToDevice) != hipSuccess)
         rc = SLBM_EHIP;
-    if (!rc && hipHostMalloc((void**)&b->h_status, 2 * count * sizeof(Status), hipHostMallocDefault) != hipSuccess)
+    if (!rc && hipHostMalloc((void**)&b->h_status, 4 * count * sizeof(Status), hipHostMallocDefault) != hipSuccess)
         rc = SLBM_EHIP;
-    if (!rc && (hipEventCreate(&b->ev[0]) != hipSuccess || hipEventCreate(&b->ev[1]) != hipSuccess ||
-                hipEventCreate(&b->t0) != hipSuccess || hipEventCreate(&b->t1) != hipSuccess ||
+    for (hipEvent_t& e : b->ev)
+        if (!rc && hipEventCreate(&e) != hipSuccess) rc = SLBM_EHIP;
+    if (!rc && (hipEventCreate(&b->t0) != hipSuccess || hipEventCreate(&b->t1) != hipSuccess ||
                 hipEventCreate(&b->pev) != hipSuccess))
         rc = SLBM_EHIP;
     // persistent path: per-instance constants and state, control block, capture stream
@@ -3155,12 +3315,12 @@ void solid_lbm_batch_destroy(slbm_batch* b)
     if (!b) return;
     if (b->stream) (void)hipStreamSynchronize(b->stream);
     else (void)hipDeviceSynchronize();
-    for (auto* c : b->ctx) solid_lbm_destroy(c);
     if (b->pstream) (void)hipStreamSynchronize(b->pstream);
+    for (auto* c : b->ctx) solid_lbm_destroy(c);
     for (void* p : b->allocs) (void)hipFree(p);
     if (b->h_status) (void)hipHostFree(b->h_status);
     if (b->h_pctl) (void)hipHostFree(b->h_pctl);
-    for (hipEvent_t e : {b->ev[0], b->ev[1], b->t0, b->t1, b->pev})
+    for (hipEvent_t e : {b->ev[0], b->ev[1], b->ev[2], b->ev[3], b->t0, b->t1, b->pev})
         if (e) (void)hipEventDestroy(e);
     if (b->pstream) (void)hipStreamDestroy(b->pstream);
     delete b;

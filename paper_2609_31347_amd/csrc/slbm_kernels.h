@@ -1525,9 +1525,20 @@ namespace slbm {
 // ---------------------------------------------------------------- batched sweeps
 // Many independent problems advance in one launch.  A block table maps every
 // block of the launch to (instance, local block / strip); each instance keeps
-// its own buffers, parameters, residual checks and stop flag.  Periodic and
-// plate instances keep separate buffer parities (fused launches flip a buffer
-// once per T steps, single-step launches once per step).
+// its own buffers, parameters, step counter, residual checks and stop flag.  A
+// launch runs the instances that its arguments name, each from the buffer of
+// its own parity; the blocks of the others return at once.
+constexpr int kMaxBatch = 128;
+struct BatchSel {
+    uint64_t act[2];      // instances that take part
+    uint64_t par[2];      // buffer that holds an instance's input
+};
+struct BatchSteps {
+    uint8_t n[kMaxBatch]; // sweeps of each instance (tiled launches)
+};
+struct BatchTimes {
+    int64_t t[kMaxBatch]; // step of each instance's check
+};
 struct BatchInst {
     SweepArgs prim[2];    // primal args by buffer parity (src = buffer p, dst = buffer p^1)
     SweepArgs adj[2];     // adjoint args by buffer parity
@@ -1542,32 +1553,30 @@ struct BatchInst {
     int64_t nblk;         // blocks of one single-step sweep
 };
 
-__device__ __forceinline__ bool mask_bit(uint64_t lo, uint64_t hi, int i)
-{
-    return i < 64 ? ((lo >> i) & 1ull) : ((hi >> (i - 64)) & 1ull);
-}
+__device__ __forceinline__ bool mask_bit(const uint64_t (&m)[2], int i) { return (m[i >> 6] >> (i & 63)) & 1ull; }
 
 template <bool ADJ>
 __global__ __launch_bounds__(kBlock) void k_sweep_batch(const BatchInst* __restrict__ inst,
-                                                       const int2* __restrict__ table, int par_periodic,
-                                                       int par_plate, uint64_t check_lo, uint64_t check_hi)
+                                                       const int2* __restrict__ table, BatchSel sel,
+                                                       BatchSel checks)
 {
     const int2 e = table[blockIdx.x];
+    if (!mask_bit(sel.act, e.x)) return;
     const BatchInst& I = inst[e.x];
     if (I.status->stop) return;
-    const int par = I.tiled ? par_plate : par_periodic;   // parity of the tiled / wave-strip class
+    const int par = mask_bit(sel.par, e.x);
     const SweepArgs& a = ADJ ? I.adj[par] : I.prim[par];
-    const bool check = mask_bit(check_lo, check_hi, e.x);
+    const bool check = mask_bit(checks.act, e.x);
     const int64_t n = (int64_t)e.y * kBlock + threadIdx.x;
     double num = 0.0, den = 0.0;
     if (n < a.N) {
-        const int sel = (I.masked ? 4 : 0) | (I.efield ? 2 : 0) | (check ? 1 : 0);
+        const int kind = (I.masked ? 4 : 0) | (I.efield ? 2 : 0) | (check ? 1 : 0);
 #define BN_CASE(i, M, EF, CH)                                                       \
     case i:                                                                         \
         if (ADJ) adjoint_node<M, EF, CH>(a, n, I.inv_nx, num, den);                 \
         else primal_node<M, EF, CH>(a, n, I.inv_nx, num, den);                      \
         break;
-        switch (sel) {
+        switch (kind) {
             BN_CASE(0, false, false, false)
             BN_CASE(1, false, false, true)
             BN_CASE(2, false, true, false)
@@ -1584,29 +1593,33 @@ __global__ __launch_bounds__(kBlock) void k_sweep_batch(const BatchInst* __restr
 
 template <int T, bool ADJ>
 __global__ __launch_bounds__(64) void k_sweep_tb_batch(const BatchInst* __restrict__ inst,
-                                                      const int2* __restrict__ table, int par_periodic)
+                                                      const int2* __restrict__ table, BatchSel sel)
 {
     const int2 e = table[blockIdx.x];
+    if (!mask_bit(sel.act, e.x)) return;
     const BatchInst& I = inst[e.x];
     if (I.status->stop) return;
-    const TBArgs a = ADJ ? I.tadj[par_periodic] : I.tprim[par_periodic];
+    const int par = mask_bit(sel.par, e.x);
+    const TBArgs a = ADJ ? I.tadj[par] : I.tprim[par];
     tb_strip<T, ADJ>(a, e.y % I.sx, e.y / I.sx);
 }
 
-// Tiled instances of a batch: `steps` <= halo sweeps of every listed tile.
+// Tiled instances of a batch: steps.n[instance] <= halo sweeps of its tiles.
 template <bool ADJ>
 __global__ __launch_bounds__(kTileBlock) void k_sweep_tile_batch(const BatchInst* __restrict__ inst,
-                                                                 const int2* __restrict__ table, int par,
-                                                                 int steps)
+                                                                 const int2* __restrict__ table, BatchSel sel,
+                                                                 BatchSteps steps)
 {
     const int2 e = table[blockIdx.x];
+    if (!mask_bit(sel.act, e.x)) return;
     const BatchInst& I = inst[e.x];
     if (I.status->stop) return;
     extern __shared__ __align__(16) double lds[];
+    const int par = mask_bit(sel.par, e.x);
     TileArgs a = ADJ ? I.ladj[par] : I.lprim[par];
-    a.steps = steps;
-    const int sel = (I.masked ? 2 : 0) | (I.efield ? 1 : 0) | (a.plan ? 4 : 0);
-    switch (sel) {
+    a.steps = steps.n[e.x];
+    const int kind = (I.masked ? 2 : 0) | (I.efield ? 1 : 0) | (a.plan ? 4 : 0);
+    switch (kind) {
         case 0: tile_body<false, false, ADJ>(a, e.y, lds); break;
         case 1: tile_body<false, true, ADJ>(a, e.y, lds); break;
         case 2: tile_body<true, false, ADJ>(a, e.y, lds); break;
@@ -1620,11 +1633,11 @@ __global__ __launch_bounds__(kTileBlock) void k_sweep_tile_batch(const BatchInst
 
 // One block per instance: instances flagged in the mask test their residual.
 __global__ __launch_bounds__(kBlock) void k_residual_batch(const BatchInst* __restrict__ inst, int adjoint,
-                                                          uint64_t check_lo, uint64_t check_hi, double tol,
-                                                          int64_t t)
+                                                          BatchSel checks, double tol, BatchTimes times)
 {
     const int i = blockIdx.x;
-    if (!mask_bit(check_lo, check_hi, i)) return;
+    if (!mask_bit(checks.act, i)) return;
+    const int64_t t = times.t[i];
     const BatchInst& I = inst[i];
     Status* st = I.status;
     if (st->stop) return;
@@ -1682,7 +1695,6 @@ __global__ void k_status_reset_all(Status* st, int n)
 // not complete within kPersistSpin polls sets the error flag and the launch
 // ends (the host reports an error) instead of hanging.
 constexpr int kPersistBlock = 1024;
-constexpr int kMaxBatch = 128;
 constexpr long kPersistSpin = 1L << 26;     // about 4 s of 64-cycle sleeps
 enum { PS_RUN = 0, PS_RESID = 1, PS_DONE = 2 };
 enum { PT_NONE = 0, PT_FUSED = 1, PT_SINGLE = 2, PT_CHECK = 3, PT_RESID = 4 };
