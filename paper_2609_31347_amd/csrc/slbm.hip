@@ -931,7 +931,8 @@ void launch_region(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, con
 
 // ---------------------------------------------------------------- tangent solves
 int64_t control_len(const slbm_ctx* c);
-int dot(slbm_ctx* c, const double* a, const double* w, int64_t n, double* out_host);
+int means_device(slbm_ctx* c, const double* a, const double** means);
+int check_control_device(slbm_ctx* c, const double* control, int64_t len, const char* what);
 
 int tangent_buffers(slbm_ctx* c)
 {
@@ -956,14 +957,19 @@ int tangent_direction(slbm_ctx* c, const double* dir, int ptr_kind, bool* use_gd
 {
     const int64_t len = control_len(c);
     if (!dir) return fail(c, SLBM_EINVAL, "direction is NULL");
-    std::vector<double> h(len);
-    if (ptr_kind == SLBM_PTR_DEVICE) {
+    const bool field = c->kind == SLBM_CTRL_FORCE_NODAL || c->kind == SLBM_CTRL_E_NODAL;
+    const bool on_device = field && ptr_kind == SLBM_PTR_DEVICE;
+    std::vector<double> h(on_device ? 0 : len);
+    if (on_device) {
+        int rc = check_control_device(c, dir, len, "direction");
+        if (rc) return rc;
+    } else if (ptr_kind == SLBM_PTR_DEVICE) {
         HIPCHK(c, hipMemcpyAsync(h.data(), dir, len * sizeof(double), hipMemcpyDeviceToHost, c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
     } else {
         std::memcpy(h.data(), dir, len * sizeof(double));
     }
-    if (!finite_all(h.data(), len)) return fail(c, SLBM_ENONFINITE, "direction has non-finite entries");
+    if (!on_device && !finite_all(h.data(), len)) return fail(c, SLBM_ENONFINITE, "direction has non-finite entries");
     *use_gdot = *use_Edot = false;
     *E0dot = 0.0;
     switch (c->kind) {
@@ -980,27 +986,25 @@ int tangent_direction(slbm_ctx* c, const double* dir, int ptr_kind, bool* use_gd
             *use_gdot = true;
             break;
         case SLBM_CTRL_FORCE_NODAL: {
-            HIPCHK(c, hipMemcpyAsync(c->tdir, h.data(), len * sizeof(double), hipMemcpyHostToDevice, c->stream));
+            const double* F = dir;
+            if (!on_device) {
+                HIPCHK(c, hipMemcpyAsync(c->tdir, h.data(), len * sizeof(double), hipMemcpyHostToDevice, c->stream));
+                F = c->tdir;
+            }
             const double* mean = nullptr;
             if (c->project) {
-                double m[2];
-                for (int k = 0; k < 2; ++k) {
-                    int rc = dot(c, c->tdir + k * c->N, nullptr, c->N, &m[k]);
-                    if (rc) return rc;
-                    m[k] /= (double)c->N;
-                }
-                HIPCHK(c, hipMemcpyAsync(c->work, m, 2 * sizeof(double), hipMemcpyHostToDevice, c->stream));
-                HIPCHK(c, hipStreamSynchronize(c->stream));
-                mean = c->work;
+                int rc = means_device(c, F, &mean);
+                if (rc) return rc;
             }
-            hipLaunchKernelGGL(k_axpb2, dim3(grid_of(2 * c->N)), dim3(kBlock), 0, c->stream, c->tdir, mean,
+            hipLaunchKernelGGL(k_axpb2, dim3(grid_of(2 * c->N)), dim3(kBlock), 0, c->stream, F, mean,
                                c->masked ? c->code : (const int32_t*)nullptr, c->N, c->dx2, c->gdot);
             HIPCHK(c, hipGetLastError());
             *use_gdot = true;
             break;
         }
         case SLBM_CTRL_E_NODAL:
-            HIPCHK(c, hipMemcpyAsync(c->Edot, h.data(), len * sizeof(double), hipMemcpyHostToDevice, c->stream));
+            HIPCHK(c, hipMemcpyAsync(c->Edot, on_device ? dir : h.data(), len * sizeof(double),
+                                     on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->stream));
             *use_Edot = true;
             break;
         default:  // E = alpha^2
@@ -1263,24 +1267,67 @@ int run_loop(slbm_ctx* c, bool adjoint, int start, int64_t last, bool use_tol, i
 
 int sum_partials(slbm_ctx* c, double* out_host)
 {
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kBlock), 0, c->stream, c->partial, c->nblk, c->scal);
+    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kBlock), 0, c->stream, c->partial, c->nblk, c->scal,
+                       1.0);
     HIPCHK(c, hipGetLastError());
     HIPCHK(c, hipMemcpyAsync(out_host, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     return SLBM_OK;
 }
 
-// sum_i a[i] * w[i] over n entries (w null: plain sum), deterministic
-int dot(slbm_ctx* c, const double* a, const double* w, int64_t n, double* out_host)
+// out[0] (device) = sum_i a[i] * w[i] / div over n entries (w null: plain sum), deterministic
+int dot_device(slbm_ctx* c, const double* a, const double* w, int64_t n, double div, double* out)
 {
     int64_t nb = (n + kBlock - 1) / kBlock;
     if (nb > c->pcap) return fail(c, SLBM_EINVAL, "internal: reduction too large");
     hipLaunchKernelGGL(k_dot_partial, dim3((unsigned)nb), dim3(kBlock), 0, c->stream, a, w, n, c->partial);
     HIPCHK(c, hipGetLastError());
-    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kBlock), 0, c->stream, c->partial, nb, c->scal);
+    hipLaunchKernelGGL(k_sum_partials, dim3(1), dim3(kBlock), 0, c->stream, c->partial, nb, out, div);
     HIPCHK(c, hipGetLastError());
+    return SLBM_OK;
+}
+
+// the same to the host
+int dot(slbm_ctx* c, const double* a, const double* w, int64_t n, double* out_host)
+{
+    int rc = dot_device(c, a, w, n, 1.0, c->scal);
+    if (rc) return rc;
     HIPCHK(c, hipMemcpyAsync(out_host, c->scal, sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
+    return SLBM_OK;
+}
+
+// Means of the two components of a, left on the device (no host round trip).
+constexpr int kScalMeans = 64, kScalFlags = 68, kScalWords = 72;   // c->scal: up to 64 sums, means, control flags
+int means_device(slbm_ctx* c, const double* a, const double** means)
+{
+    int rc;
+    for (int k = 0; k < 2; ++k)
+        if ((rc = dot_device(c, a + k * c->N, nullptr, c->N, (double)c->N, c->scal + kScalMeans + k))) return rc;
+    *means = c->scal + kScalMeans;
+    return SLBM_OK;
+}
+
+// Tests a control (or, with what = "direction", its derivative) in device
+// memory before anything changes; one small read-back.
+int check_control_device(slbm_ctx* c, const double* control, int64_t len, const char* what)
+{
+    const bool moduli = c->kind == SLBM_CTRL_E_NODAL && std::strcmp(what, "control") == 0;
+    unsigned long long* flags = reinterpret_cast<unsigned long long*>(c->scal + kScalFlags);
+    hipLaunchKernelGGL(k_control_reset, dim3(1), dim3(64), 0, c->stream, flags);
+    const unsigned blocks = (unsigned)std::min<int64_t>((len + kBlock - 1) / kBlock, 4096);
+    hipLaunchKernelGGL(k_control_check, dim3(blocks), dim3(kBlock), 0, c->stream, control, len, moduli ? 1 : 0,
+                       c->masked ? 1 : 0, c->nu, flags);
+    HIPCHK(c, hipGetLastError());
+    unsigned long long first[3];
+    HIPCHK(c, hipMemcpyAsync(first, flags, sizeof(first), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    if (first[CTL_NONFINITE] != ~0ull)
+        return fail(c, SLBM_ENONFINITE, std::string(what) + " has non-finite entries");
+    if (moduli && first[CTL_NONPOSITIVE] < first[CTL_GAMMA])
+        return fail(c, SLBM_EINVAL, "E control must be > 0 everywhere");
+    if (moduli && first[CTL_GAMMA] != ~0ull)
+        return fail(c, SLBM_EINVAL, "tau_s = tau_f: the boundary coefficient gamma is undefined");
     return SLBM_OK;
 }
 
@@ -1312,19 +1359,26 @@ int64_t control_len(const slbm_ctx* c)
 }
 
 // Control -> forcing / moduli (eq. forcing, eq. zero_mean_projection,
-// eq. E_substitution).  The control is staged in c->ctrl.
+// eq. E_substitution).
 int apply_control(slbm_ctx* c, const double* control, int ptr_kind)
 {
     int64_t len = control_len(c);
     if (!control) return fail(c, SLBM_EINVAL, "control is NULL");
-    std::vector<double> h(len);
+    // whole fields in device memory are tested there; their copies stay on the device
+    const bool field = c->kind == SLBM_CTRL_FORCE_NODAL || c->kind == SLBM_CTRL_E_NODAL;
+    const bool on_device = field && ptr_kind == SLBM_PTR_DEVICE;
+    std::vector<double> h(on_device ? 1 : len);
     if (ptr_kind == SLBM_PTR_DEVICE) {
-        HIPCHK(c, hipMemcpyAsync(h.data(), control, len * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+        HIPCHK(c, hipMemcpyAsync(h.data(), control, h.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+        if (on_device) {
+            int rc = check_control_device(c, control, len, "control");
+            if (rc) return rc;
+        }
         HIPCHK(c, hipStreamSynchronize(c->stream));
     } else {
         std::memcpy(h.data(), control, len * sizeof(double));
     }
-    if (!finite_all(h.data(), len)) return fail(c, SLBM_ENONFINITE, "control has non-finite entries");
+    if (!on_device && !finite_all(h.data(), len)) return fail(c, SLBM_ENONFINITE, "control has non-finite entries");
     switch (c->kind) {
         case SLBM_CTRL_FORCE_MODES: {
             HIPCHK(c, hipMemcpyAsync(c->ctrl, h.data(), len * sizeof(double), hipMemcpyHostToDevice, c->stream));
@@ -1341,20 +1395,17 @@ int apply_control(slbm_ctx* c, const double* control, int ptr_kind)
             break;
         }
         case SLBM_CTRL_FORCE_NODAL: {
-            HIPCHK(c, hipMemcpyAsync(c->ctrl, h.data(), len * sizeof(double), hipMemcpyHostToDevice, c->stream));
+            const double* F = control;
+            if (!on_device) {
+                HIPCHK(c, hipMemcpyAsync(c->ctrl, h.data(), len * sizeof(double), hipMemcpyHostToDevice, c->stream));
+                F = c->ctrl;
+            }
             const double* mean = nullptr;
             if (c->project) {
-                double m[2];
-                for (int k = 0; k < 2; ++k) {
-                    int rc = dot(c, c->ctrl + k * c->N, nullptr, c->N, &m[k]);
-                    if (rc) return rc;
-                    m[k] /= (double)c->N;
-                }
-                HIPCHK(c, hipMemcpyAsync(c->work, m, 2 * sizeof(double), hipMemcpyHostToDevice, c->stream));
-                HIPCHK(c, hipStreamSynchronize(c->stream));
-                mean = c->work;
+                int rc = means_device(c, F, &mean);
+                if (rc) return rc;
             }
-            hipLaunchKernelGGL(k_axpb2, dim3(grid_of(2 * c->N)), dim3(kBlock), 0, c->stream, c->ctrl, mean,
+            hipLaunchKernelGGL(k_axpb2, dim3(grid_of(2 * c->N)), dim3(kBlock), 0, c->stream, F, mean,
                                c->masked ? c->code : (const int32_t*)nullptr, c->N, c->dx2, c->g);
             HIPCHK(c, hipGetLastError());
             c->E_cur = c->E;
@@ -1362,13 +1413,13 @@ int apply_control(slbm_ctx* c, const double* control, int ptr_kind)
             break;
         }
         case SLBM_CTRL_E_NODAL: {
-            for (int64_t i = 0; i < len; ++i) {
+            for (int64_t i = 0; i < len && !on_device; ++i) {
                 if (!(h[i] > 0.0)) return fail(c, SLBM_EINVAL, "E control must be > 0 everywhere");
                 if (c->masked && !gamma_ok(h[i], c->nu))
                     return fail(c, SLBM_EINVAL, "tau_s = tau_f: the boundary coefficient gamma is undefined");
             }
-            HIPCHK(c, hipMemcpyAsync(c->Efield, h.data(), len * sizeof(double), hipMemcpyHostToDevice,
-                                     c->stream));
+            HIPCHK(c, hipMemcpyAsync(c->Efield, on_device ? control : h.data(), len * sizeof(double),
+                                     on_device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice, c->stream));
             HIPCHK(c, hipMemcpyAsync(c->g, c->fixedF, 2 * c->N * sizeof(double), hipMemcpyDeviceToDevice,
                                      c->stream));
             c->efield_on = true;
@@ -1481,16 +1532,11 @@ int adjoint_prepare(slbm_ctx* c)
 int project_source(slbm_ctx* c)
 {
     if (c->masked) return SLBM_OK;
-    double m[2];
-    int rc;
-    for (int k = 0; k < 2; ++k) {
-        if ((rc = dot(c, c->asrc + k * c->N, nullptr, c->N, &m[k]))) return rc;
-        m[k] /= (double)c->N;
-    }
-    HIPCHK(c, hipMemcpyAsync(c->work, m, 2 * sizeof(double), hipMemcpyHostToDevice, c->stream));
-    HIPCHK(c, hipStreamSynchronize(c->stream));
+    const double* mean;
+    int rc = means_device(c, c->asrc, &mean);
+    if (rc) return rc;
     hipLaunchKernelGGL(k_axpb2, dim3(grid_of(2 * c->N)), dim3(kBlock), 0, c->stream, c->asrc,
-                       (const double*)c->work, (const int32_t*)nullptr, c->N, 1.0, c->asrc);
+                       mean, (const int32_t*)nullptr, c->N, 1.0, c->asrc);
     HIPCHK(c, hipGetLastError());
     return SLBM_OK;
 }
@@ -1570,29 +1616,16 @@ int assemble_grad(slbm_ctx* c, double* grad, int ptr_kind)
     int rc;
     switch (c->kind) {
         case SLBM_CTRL_FORCE_MODES: {
-            std::vector<double> h(c->nmodes);
-            for (int m = 0; m < c->nmodes; ++m)
-                if ((rc = dot(c, c->dJdF, c->modes + (int64_t)m * 2 * c->N, 2 * c->N, &h[m]))) return rc;
-            if (ptr_kind == SLBM_PTR_DEVICE) {
-                HIPCHK(c, hipMemcpyAsync(grad, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice,
-                                         c->stream));
-                HIPCHK(c, hipStreamSynchronize(c->stream));
-            } else {
-                std::memcpy(grad, h.data(), h.size() * sizeof(double));
-            }
-            return SLBM_OK;
+            for (int m = 0; m < c->nmodes; ++m)          // at most 64 modes: c->scal
+                if ((rc = dot_device(c, c->dJdF, c->modes + (int64_t)m * 2 * c->N, 2 * c->N, 1.0, c->scal + m))) return rc;
+            return copy_out(c, grad, c->scal, c->nmodes * sizeof(double), ptr_kind);
         }
         case SLBM_CTRL_FORCE_NODAL: {
             if (c->project) {
-                double m[2];
-                for (int k = 0; k < 2; ++k) {
-                    if ((rc = dot(c, c->dJdF + k * c->N, nullptr, c->N, &m[k]))) return rc;
-                    m[k] /= (double)c->N;
-                }
-                HIPCHK(c, hipMemcpyAsync(c->work, m, 2 * sizeof(double), hipMemcpyHostToDevice, c->stream));
-                HIPCHK(c, hipStreamSynchronize(c->stream));
+                const double* mean;
+                if ((rc = means_device(c, c->dJdF, &mean))) return rc;
                 hipLaunchKernelGGL(k_axpb2, dim3(grid_of(2 * c->N)), dim3(kBlock), 0, c->stream, c->dJdF,
-                                   (const double*)c->work, (const int32_t*)nullptr, c->N, 1.0, c->dJdF);
+                                   mean, (const int32_t*)nullptr, c->N, 1.0, c->dJdF);
                 HIPCHK(c, hipGetLastError());
             }
             return copy_out(c, grad, c->dJdF, 2 * c->N * sizeof(double), ptr_kind);
@@ -1789,7 +1822,7 @@ int solid_lbm_init(const slbm_problem* p, slbm_ctx** out)
     A(&c->Efield, P1);
     A(&c->fixedF, P2);
     A(&c->partial, (size_t)c->pcap * 2 * sizeof(double));
-    A(&c->scal, 64);
+    A(&c->scal, kScalWords * sizeof(double));
     A(&c->ctrl, (size_t)std::max<int64_t>(2 * N, 64) * sizeof(double));
     A(&c->status, sizeof(Status));
     if (c->kind == SLBM_CTRL_FORCE_MODES) A(&c->modes, (size_t)c->nmodes * P2);
