@@ -1034,6 +1034,31 @@ void launch_tangent(slbm_ctx* c, const TangentArgs& a, bool check)
 #undef TG_CASE
 }
 
+// Tile of the fused tangent launches: the most steps (7, 5, 3) whose tiles fit
+// the compute units at once, else 3.
+TangentTile tangent_tile(const slbm_ctx* c)
+{
+    TangentTile t;
+    const int64_t cus = c->simds / 4;
+    for (int h : {7, 5, 3}) {
+        t.halo = t.steps = h;
+        t.t = kTanSide - 2 * h;
+        t.tiles_x = (c->nx + t.t - 1) / t.t;
+        if ((int64_t)t.tiles_x * ((c->ny + t.t - 1) / t.t) <= cus) break;
+    }
+    return t;
+}
+
+void launch_tangent_tile(slbm_ctx* c, const TangentArgs& a, const TangentTile& t)
+{
+    const dim3 grid((unsigned)(t.tiles_x * ((c->ny + t.t - 1) / t.t))), block(kTanBlock);
+    const size_t lds = (size_t)16 * (t.t + 2 * t.halo) * (t.t + 2 * t.halo) * sizeof(double);
+    if (c->masked && c->efield_on) hipLaunchKernelGGL((k_tangent_tile<true, true>), grid, block, lds, c->stream, a, t);
+    else if (c->masked) hipLaunchKernelGGL((k_tangent_tile<true, false>), grid, block, lds, c->stream, a, t);
+    else if (c->efield_on) hipLaunchKernelGGL((k_tangent_tile<false, true>), grid, block, lds, c->stream, a, t);
+    else hipLaunchKernelGGL((k_tangent_tile<false, false>), grid, block, lds, c->stream, a, t);
+}
+
 // Tangent iteration from zero (value and derivative), checks every K steps;
 // returns the final step t, the buffer X holding the input of step t, the
 // last residual and whether the test passed.
@@ -1045,15 +1070,18 @@ int tangent_loop(slbm_ctx* c, const TangentArgs& base, int64_t* t_out, int* x_ou
     const bool use_tol = c->tol > 0.0;
     const int64_t K = c->K, last = c->max_steps;
     TangentArgs a = base;
+    TangentTile tile = tangent_tile(c);
     int cur = 0, last_in = 0;
     int64_t chunk = 0;
     int64_t s = 0;
     bool stopped = false;
     CheckLog checks;
+    const int64_t poll = std::min<int64_t>(K * (CheckLog::kKeep / 4), kPollSteps);
     auto last_report = std::chrono::steady_clock::now();
     HIPCHK(c, hipEventRecord(c->t0, c->stream));
     while (s <= last && !stopped) {
-        int64_t end = use_tol ? std::min(last, (s / K + 1) * K - 1) : last;
+        // a chunk ends before a check; short intervals are polled several at a time
+        int64_t end = use_tol ? std::min(last, ((s + poll) / K + 1) * K - 1) : last;
         if (!use_tol && end - s > 4096) end = s + 4095;
         while (s <= end) {
             const bool check = use_tol && s > 0 && s % K == 0;
@@ -1061,6 +1089,15 @@ int tangent_loop(slbm_ctx* c, const TangentArgs& base, int64_t* t_out, int* x_ou
             a.srcd = c->td[cur];
             a.dstv = c->tv[cur ^ 1];
             a.dstd = c->td[cur ^ 1];
+            int64_t plain = std::min(end, last - 1) - s + 1;         // no check among them but at s, never the last step
+            if (use_tol) plain = std::min(plain, (s / K + 1) * K - s);
+            if (!check && plain >= 2) {
+                tile.steps = (int)std::min<int64_t>(plain, tile.halo);
+                launch_tangent_tile(c, a, tile);
+                cur ^= 1;
+                s += tile.steps;
+                continue;
+            }
             launch_tangent(c, a, check);
             if (check) {
                 hipLaunchKernelGGL(k_residual2, dim3(1), dim3(kBlock), 0, c->stream, c->tpart, c->nblk, c->status,
