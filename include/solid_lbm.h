@@ -280,10 +280,11 @@ int solid_lbm_time_sweeps(slbm_ctx *ctx, int32_t adjoint, int64_t n, double *ms)
  * them the LDS tiles: 8 steps up to 131072 nodes, above the most of 6, 5, 4, 3
  * whose (32 - 2 steps)^2 tiles number no more than the compute units, else 6);
  * larger periodic grids take register panels (6 .. 12 steps) while a shape of
- * them fits the compute units at once, and, with a uniform material, the
- * wave-strip kernel with 8 steps beyond, with as many rows per wave as keep the wave count at or
- * below the device's SIMD count.  rows_per_wave: rows each wave of a wave-strip launch
- * covers (0 = automatic).  Every setting gives the same result bit for bit:
+ * them fits the compute units at once, and, with a uniform material, a pipeline
+ * of 8 waves with 16 steps beyond (fewer steps before a check: wave strips; all
+ * wave strips of 8 steps if rows_per_wave is set).  rows_per_wave: rows each
+ * wave of a wave-strip launch covers (0 = automatic: as many as keep the wave
+ * count at or below the device's SIMD count).  Every setting gives the same result bit for bit:
  * a fused launch performs exactly the arithmetic of its single sweeps.
  * SLBM_EINVAL if the value is out of range, or if a tile set by
  * solid_lbm_set_tiles would not fit with a halo of steps_per_launch. */

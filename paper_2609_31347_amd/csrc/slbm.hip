@@ -15,6 +15,7 @@
 
 #include "solid_lbm.h"
 #include "slbm_panel.h"
+#include "slbm_pipe.h"
 
 using namespace slbm;
 
@@ -366,7 +367,7 @@ int fused_rows(const slbm_ctx* c, int T)
     return std::min(H, c->ny);
 }
 
-void launch_fused(slbm_ctx* c, bool adjoint, const SweepArgs& s, int T)
+TBArgs strip_args(const slbm_ctx* c, const SweepArgs& s)
 {
     TBArgs a;
     a.src = s.src;
@@ -380,6 +381,12 @@ void launch_fused(slbm_ctx* c, bool adjoint, const SweepArgs& s, int T)
     a.ks = s.ks;
     a.kd = s.kd;
     a.scale = s.scale;
+    return a;
+}
+
+void launch_fused(slbm_ctx* c, bool adjoint, const SweepArgs& s, int T)
+{
+    TBArgs a = strip_args(c, s);
     a.H = fused_rows(c, T);
     int V = 64 - 2 * T;
     a.strips = (c->nx + V - 1) / V;
@@ -657,7 +664,8 @@ constexpr size_t kPlateLds = (kPanelEdge + 8 * kPanelCap) * sizeof(double);
 
 // The fused launches of a solve loop.
 struct Fuse {
-    int T = 1;        // steps per wave-strip launch
+    int T = 1;        // steps per wave-strip or pipeline launch
+    int H = 0;        // rows per workgroup of the pipeline (0: wave strips)
     int TL = 1;       // steps per launch of LDS tiles or panels
     int R = 0;        // rows per lane of the panels (0: LDS tiles)
     int tiles = 0;    // LDS tiles of a planned launch, whose first sweep may be a residual check (0: none)
@@ -673,20 +681,21 @@ int panel_tiles(const slbm_ctx* c, int R, int h)
 // unit, so a shape is good while its regions fit the compute units in one
 // round.  The shapes in order of their time per step in one round (us per
 // step, uniform material, 100 - 250 workgroups): (R, h) = (3, 6) 1.6, (4, 8)
-// 1.7, (4, 7) 1.85, (6, 12) 1.88, (6, 10) 2.1, (8, 12) 2.4, (6, 8) 2.4, (8, 8)
-// 3.0; the first that fits is taken.  Grids whose 16 x 16 LDS tiles fit in one
+// 1.7, (4, 7) 1.85, (6, 12) 1.88, (6, 10) 2.1, (8, 12) 2.4, (6, 8) 2.4; the
+// first that fits is taken.  Grids whose 16 x 16 LDS tiles fit in one
 // round keep those (256^2: 1.32 against 1.54 with (3, 6)).  Beyond one round
-// uniform problems take the wave strips (800^2: 4.14 us per step against 4.25
-// with panels of (8, 7) and 4.6 in several rounds; 1024^2: 5.2 against 6.5).
-// E fields have no strips and go on with (3, 6) in several rounds (against
-// LDS tiles: 700 x 651 6.4 -> 4.1, 1024^2 13.3 -> 6.8).  (8, h) spills with a
-// modulus per node, so E fields do not take it.
+// uniform problems take the pipeline (700^2: 3.21 us per step against 3.37 with
+// panels of (8, 8), which fit to 768^2; 800^2: 3.6 against 4.25 with (8, 7);
+// 600^2: 2.98 against 2.62 with (8, 12)).  E fields have no pipeline and go on
+// with (3, 6) in several rounds (against LDS tiles: 700 x 651 6.4 -> 4.1,
+// 1024^2 13.3 -> 6.8).  (8, 12) spills with a modulus per node, so E fields do
+// not take it.
 bool panel_shape(const slbm_ctx* c, Fuse* f)
 {
     if (c->masked || c->tb_T >= 0 || c->tile_w > 0) return false;
     const int cus = c->simds / 4;
     if ((int64_t)((c->nx + 15) / 16) * ((c->ny + 15) / 16) <= cus) return false;
-    static const int shapes[8][2] = {{3, 6}, {4, 8}, {4, 7}, {6, 12}, {6, 10}, {8, 12}, {6, 8}, {8, 8}};
+    static const int shapes[7][2] = {{3, 6}, {4, 8}, {4, 7}, {6, 12}, {6, 10}, {8, 12}, {6, 8}};
     for (const auto& s : shapes) {
         if (c->efield_on && s[0] == 8) continue;
         if (panel_tiles(c, s[0], s[1]) > cus) continue;
@@ -896,6 +905,81 @@ int build_panel_plan(slbm_ctx* c, int R, int h)
     return SLBM_OK;
 }
 
+// ---------------------------------------------------------------- wave pipelines
+constexpr int kPipeL = 2, kPipeS = 8, kPipeT = kPipeL * kPipeS;   // levels per wave, waves, steps per launch
+typedef void (*pipe_fn)(TBArgs);
+pipe_fn pipe_kernel(bool adjoint, bool even)
+{
+    if (adjoint) return even ? k_sweep_pipe<kPipeL, kPipeS, true, true> : k_sweep_pipe<kPipeL, kPipeS, true, false>;
+    return even ? k_sweep_pipe<kPipeL, kPipeS, false, true> : k_sweep_pipe<kPipeL, kPipeS, false, false>;
+}
+
+// Automatic shape of uniform periodic grids beyond one round of panels.  A
+// workgroup (8 waves, 140 KiB of LDS) fills a compute unit and takes 0.92 -
+// 0.95 us per row, for its H rows, 2 T halo rows and the pipeline's filling;
+// the row blocks that take the fewest such steps are chosen (2048^2: 242
+// workgroups of 187 rows).  A wave strip of 8 steps takes 1.0 - 1.1 us per row
+// for its rows and 16 halo rows; the pipeline is taken up to 2.3 times its
+// steps.  us per step, strips -> pipeline: 700^2 3.4 -> 3.2, 800^2 3.9 -> 3.6,
+// 1025 x 777 4.4 -> 4.15, 1024^2 5.1 -> 4.5, 1500 x 1501 10.3 -> 7.5, 2048^2
+// 19.0 -> 13.4, 4096^2 77 -> 50, 96 x 8192 4.1 -> 3.7, 20000 x 100 10.2 -> 7.4;
+// flat grids have more halo than rows: 16384 x 40 4.2 -> 4.05, 4096 x 128 even,
+// 46669 x 3 2.1 -> 4.2.
+bool pipe_shape(const slbm_ctx* c, Fuse* f)
+{
+    if (use_tiles(c) || c->tb_T >= 0 || c->tb_H > 0) return false;
+    const int V = kPipeCols - 2 * kPipeT, cus = std::max(1, c->simds / 4);
+    const int64_t strips = (c->nx + V - 1) / V;
+    int64_t best = -1;
+    for (int blocks = 1; blocks <= std::min(c->ny, 256); ++blocks) {
+        const int H = (c->ny + blocks - 1) / blocks;
+        const int64_t wgs = strips * ((c->ny + H - 1) / H);
+        const int64_t cost = (wgs + cus - 1) / cus * (H + 2 * kPipeT + kPipeS);
+        if (best >= 0 && cost >= best) continue;
+        best = cost;
+        f->H = H;
+    }
+    const int hs = fused_rows(c, 8);
+    const int64_t waves = (int64_t)((c->nx + 47) / 48) * ((c->ny + hs - 1) / hs);
+    if (10 * best > 23 * ((waves + c->simds - 1) / c->simds * (hs + 16))) {
+        f->H = 0;
+        return false;
+    }
+    f->T = kPipeT;
+    return true;
+}
+
+int pipe_lds_limit(slbm_ctx* c)
+{
+    for (int k = 0; k < 4; ++k)
+        HIPCHK(c, hipFuncSetAttribute(reinterpret_cast<const void*>(pipe_kernel(k & 1, k & 2)),
+                                      hipFuncAttributeMaxDynamicSharedMemorySize, (int)pipe_lds_bytes<kPipeS>()));
+    return SLBM_OK;
+}
+
+// The steps of one launch of the strip loop: a whole pipeline, or, with fewer
+// steps left than its 16, wave strips of 8, 6, 4 or 2 (1: none fits).
+int strip_steps(const Fuse& f, int64_t plain)
+{
+    if (f.T > 1 && plain >= f.T) return f.T;
+    if (f.H > 0 && plain >= 2) return (int)std::min<int64_t>(8, plain & ~1);
+    return 1;
+}
+
+void launch_strips(slbm_ctx* c, bool adjoint, const SweepArgs& s, const Fuse& f, int steps)
+{
+    if (f.H == 0 || steps < kPipeT) {
+        launch_fused(c, adjoint, s, steps);
+        return;
+    }
+    TBArgs a = strip_args(c, s);
+    const int V = kPipeCols - 2 * kPipeT;
+    a.H = f.H;
+    a.strips = (c->nx + V - 1) / V;
+    hipLaunchKernelGGL(pipe_kernel(adjoint, c->nx % 2 == 0), dim3((unsigned)(a.strips * ((c->ny + a.H - 1) / a.H))),
+                       dim3(64 * kPipeS), pipe_lds_bytes<kPipeS>(), c->stream, a);
+}
+
 // Chooses the fused launches of a loop and builds what they need.
 int plan_fuse(slbm_ctx* c, Fuse* f)
 {
@@ -907,6 +991,7 @@ int plan_fuse(slbm_ctx* c, Fuse* f)
         *f = Fuse();
     }
     if (panel_shape(c, f)) return SLBM_OK;
+    if (pipe_shape(c, f)) return pipe_lds_limit(c);
     f->T = fused_steps(c);
     f->TL = tile_steps(c);
     int rc;
@@ -1211,13 +1296,13 @@ int run_loop(slbm_ctx* c, bool adjoint, int start, int64_t last, bool use_tol, i
                 s += k;
                 continue;
             }
-            if (!check && T > 1 && plain >= T) {
+            if (const int k = check ? 1 : strip_steps(fuse, plain); k > 1) {
                 a.src = bufs[cur];
                 a.dst = bufs[cur ^ 1];
-                HIPCHK(c, c->lt.before(c->stream, T, s));
-                launch_fused(c, adjoint, a, T);
+                HIPCHK(c, c->lt.before(c->stream, k, s));
+                launch_strips(c, adjoint, a, fuse, k);
                 cur ^= 1;
-                s += T;
+                s += k;
                 continue;
             }
             if (!check && TL > 1 && plain >= 2) {
@@ -2061,14 +2146,14 @@ int solid_lbm_time_sweeps(slbm_ctx* c, int32_t adjoint, int64_t n, double* ms)
         int rc = plan_fuse(c, &fuse);
         if (rc) return rc;
     }
-    const int T = fuse.T, TL = fuse.TL;
+    const int TL = fuse.TL;
     HIPCHK(c, hipEventRecord(c->t0, c->stream));
     for (int64_t s = 0; s < n;) {
         a.src = bufs[cur];
         a.dst = bufs[cur ^ 1];
-        if (T > 1 && n - s >= T) {
-            launch_fused(c, adjoint != 0, a, T);
-            s += T;
+        if (const int k = strip_steps(fuse, n - s); k > 1) {
+            launch_strips(c, adjoint != 0, a, fuse, k);
+            s += k;
         } else if (TL > 1 && n - s >= 2) {
             const int k = (int)std::min<int64_t>(n - s, TL);
             launch_region(c, adjoint != 0, a, k, fuse);

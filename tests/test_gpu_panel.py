@@ -10,7 +10,7 @@ from paper_2609_31347_amd import inputs as I
 
 pytestmark = pytest.mark.gpu
 
-# (rows per lane, halo) by size: (3,6), (4,8), (4,7), (6,12), (6,10), (8,12), (6,8), (8,8); a 40-column grid
+# (rows per lane, halo) by size: (3,6), (4,8), (4,7), (6,12), (6,10), (8,12), (6,8), the wave pipeline; a 40-column grid
 # that its 64-column regions wrap onto
 SIZES = ((300, 300), (501, 333), (448, 448), (480, 470), (512, 512), (600, 600), (192, 2048), (700, 700), (40, 5000))
 E_SIZES = ((401, 299), (501, 333), (480, 470), (700, 651))      # the last in several rounds of workgroups
