@@ -273,16 +273,16 @@ int solid_lbm_time_sweeps(slbm_ctx *ctx, int32_t adjoint, int64_t n, double *ms)
  * 1 = one time step per launch, else that many time steps fused in one
  * launch: 2, 4, 6 or 8 for periodic, uniform-material problems (wave-strip
  * kernel), 2 .. 8 for plates, E-field controls and problems given a tile by
- * solid_lbm_set_tiles (LDS-tiled kernel).  Automatic: the LDS-tiled kernel
- * with 8 steps for plates and periodic grids whose 16 x 16 tiles fit the
- * compute units at once; larger plates take register panels of 64 columns (6,
- * 8 or 10 steps, by a model of the launch; a plate whose rim is too dense for
- * them the LDS tiles: 8 steps up to 131072 nodes, above the most of 6, 5, 4, 3
- * whose (32 - 2 steps)^2 tiles number no more than the compute units, else 6);
- * larger periodic grids take register panels (6 .. 12 steps) while a shape of
- * them fits the compute units at once, and, with a uniform material, a pipeline
- * of 8 waves with 16 steps beyond (fewer steps before a check: wave strips; all
- * wave strips of 8 steps if rows_per_wave is set).  rows_per_wave: rows each
+ * solid_lbm_set_tiles (LDS-tiled kernel).  Automatic: plates whose 16 x 16
+ * tiles fit the compute units at once the LDS-tiled kernel with 8 steps; larger
+ * plates register panels of 64 columns (6, 8 or 10 steps, by a model of the
+ * launch; a plate whose rim is too dense for them the LDS tiles: 8 steps up to
+ * 131072 nodes, above the most of 6, 5, 4, 3 whose (32 - 2 steps)^2 tiles number
+ * no more than the compute units, else 6); periodic grids register panels (6 ..
+ * 14 steps) while a shape of them fits the compute units at once, and, with a
+ * uniform material, a pipeline of 8 waves with 16 steps beyond (fewer steps
+ * before a check: wave strips; all wave strips of 8 steps if rows_per_wave is
+ * set; thin grids LDS tiles or wave strips).  rows_per_wave: rows each
  * wave of a wave-strip launch covers (0 = automatic: as many as keep the wave
  * count at or below the device's SIMD count).  Every setting gives the same result bit for bit:
  * a fused launch performs exactly the arithmetic of its single sweeps.

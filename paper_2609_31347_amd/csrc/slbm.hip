@@ -330,11 +330,10 @@ struct CheckLog {
 
 // Steps fused per launch for this context (1 = single-step sweeps only): the
 // fused kernels cover the periodic, uniform-material bulk.
-// The LDS-tiled kernel serves plates and E fields always, periodic uniform
-// problems when a tile shape was set, and, with automatic tuning, periodic
-// uniform grids up to 131072 nodes that the register panels (panel_shape) do
-// not take (measured on MI355X: 128^2 1.3 vs 3.5 us per step, 256^2 1.7 vs 3.9
-// for the best wave-strip shape).
+// The LDS-tiled kernel serves plates and E fields, periodic uniform problems
+// when a tile shape was set, and, with automatic tuning, periodic uniform grids
+// up to 131072 nodes that the register panels (panel_shape) do not take: thin
+// ones, of more panels than compute units.
 constexpr int64_t kTileAutoMaxNodes = 131072;
 bool use_tiles(const slbm_ctx* c)
 {
@@ -418,7 +417,7 @@ void launch_fused(slbm_ctx* c, bool adjoint, const SweepArgs& s, int T)
 // 240 tiles, 3.0 us).  Grids of one 8 x 8 tile per compute unit that check every
 // 9 to 12 steps take the whole interval in one launch, whose first sweep is the
 // check (8 steps and the rest as a second launch: the 64 x 39 plate, K = 10,
-// 2.80 us per step against 2.44; 32 x 32, K = 12, 2.45 against 2.22).
+// 2.80 us per step against 2.44).
 int tile_halo(const slbm_ctx* c)
 {
     if (c->tb_T >= 0) return std::max(1, std::min(c->tb_T, 8));
@@ -629,13 +628,14 @@ void launch_tile(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, int h
 // ---------------------------------------------------------------- register panels
 typedef void (*panel_fn)(PanelArgs);
 template <bool E, bool A>
-panel_fn panel_of(int R)
+panel_fn panel_of(int R, bool check)
 {
     switch (R) {
-        case 3: return k_sweep_panel<E, A, 3>;
-        case 4: return k_sweep_panel<E, A, 4>;
-        case 6: return k_sweep_panel<E, A, 6>;
-        default: return E ? nullptr : k_sweep_panel<false, A, 8>;
+        case 2: return check ? k_sweep_panel<E, A, 2, 32, true> : k_sweep_panel<E, A, 2, 32, false>;
+        case 3: return k_sweep_panel<E, A, 3, 64, false>;
+        case 4: return k_sweep_panel<E, A, 4, 64, false>;
+        case 6: return k_sweep_panel<E, A, 6, 64, false>;
+        default: return E ? nullptr : k_sweep_panel<false, A, 8, 64, false>;
     }
 }
 
@@ -647,13 +647,13 @@ panel_fn plate_of(int R)
         default: return k_sweep_plate<E, A, 4>;
     }
 }
-panel_fn panel_kernel(bool masked, bool efield, bool adjoint, int R)
+panel_fn panel_kernel(bool masked, bool efield, bool adjoint, int R, bool check = false)
 {
     switch ((masked ? 4 : 0) | (efield ? 2 : 0) | (adjoint ? 1 : 0)) {
-        case 0: return panel_of<false, false>(R);
-        case 1: return panel_of<false, true>(R);
-        case 2: return panel_of<true, false>(R);
-        case 3: return panel_of<true, true>(R);
+        case 0: return panel_of<false, false>(R, check);
+        case 1: return panel_of<false, true>(R, check);
+        case 2: return panel_of<true, false>(R, check);
+        case 3: return panel_of<true, true>(R, check);
         case 4: return plate_of<false, false>(R);
         case 5: return plate_of<false, true>(R);
         case 6: return plate_of<true, false>(R);
@@ -667,23 +667,35 @@ struct Fuse {
     int T = 1;        // steps per wave-strip or pipeline launch
     int H = 0;        // rows per workgroup of the pipeline (0: wave strips)
     int TL = 1;       // steps per launch of LDS tiles or panels
-    int R = 0;        // rows per lane of the panels (0: LDS tiles)
-    int tiles = 0;    // LDS tiles of a planned launch, whose first sweep may be a residual check (0: none)
+    int R = 0;        // rows per lane of the panels (0: LDS tiles; 2: panels of 32 columns)
+    int tiles = 0;    // tiles of a launch whose first sweep may be a residual check (0: none)
 };
+
+int panel_cols(int R) { return R == 2 ? 32 : 64; }
 
 int panel_tiles(const slbm_ctx* c, int R, int h)
 {
-    const int tw = 64 - 2 * h, th = kPanelWaves * R - 2 * h;
+    const int cols = panel_cols(R);
+    const int tw = cols - 2 * h, th = kPanelWaves * (64 / cols) * R - 2 * h;
     return ((c->nx + tw - 1) / tw) * ((c->ny + th - 1) / th);
 }
 
 // Automatic panel shape of a periodic problem.  A workgroup fills a compute
 // unit, so a shape is good while its regions fit the compute units in one
-// round.  The shapes in order of their time per step in one round (us per
-// step, uniform material, 100 - 250 workgroups): (R, h) = (3, 6) 1.6, (4, 8)
-// 1.7, (4, 7) 1.85, (6, 12) 1.88, (6, 10) 2.1, (8, 12) 2.4, (6, 8) 2.4; the
-// first that fits is taken.  Grids whose 16 x 16 LDS tiles fit in one
-// round keep those (256^2: 1.32 against 1.54 with (3, 6)).  Beyond one round
+// round.  Small grids take panels of 32 columns (R = 2: regions of 32 x 32)
+// with the widest halo, 14 to 6, that still fits: more steps per launch at the
+// same cost of the launch and its loads.  us per step, LDS tiles of 8 steps (or
+// 64-column panels at 300^2) -> these, uniform material: 32^2 0.93 -> 0.69, 64^2
+// 0.93 -> 0.71, 80^2 0.95 -> 0.74, 128^2 0.95 -> 0.80, 160^2 1.12 -> 0.86, 200^2
+// 1.29 -> 1.02, 256^2 1.28 -> 1.08, 300^2 1.56 -> 1.37 (E fields alike, + 3 %);
+// taller ones (R = 3, 4, 6) were slower at every size, and a halo of 4 or 5
+// slower than 64 columns (371^2 1.85 against 1.64).  With a short check interval
+// the halo is the least that needs as many launches (K = 12: one of 12 steps,
+// whose first sweep is the check).
+// Then, in order of their time per step in one round (us per step, uniform
+// material, 100 - 250 workgroups): (R, h) = (3, 6) 1.6, (4, 8) 1.7, (4, 7) 1.85,
+// (6, 12) 1.88, (6, 10) 2.1, (8, 12) 2.4, (6, 8) 2.4; the first that fits is
+// taken (panels of 32 columns at 501 x 333: 1.89 against 1.71).  Beyond one round
 // uniform problems take the pipeline (700^2: 3.21 us per step against 3.37 with
 // panels of (8, 8), which fit to 768^2; 800^2: 3.6 against 4.25 with (8, 7);
 // 600^2: 2.98 against 2.62 with (8, 12)).  E fields have no pipeline and go on
@@ -694,7 +706,16 @@ bool panel_shape(const slbm_ctx* c, Fuse* f)
 {
     if (c->masked || c->tb_T >= 0 || c->tile_w > 0) return false;
     const int cus = c->simds / 4;
-    if ((int64_t)((c->nx + 15) / 16) * ((c->ny + 15) / 16) <= cus) return false;
+    f->T = 1;
+    for (int h = 14; h >= 6; --h) {
+        if (panel_tiles(c, 2, h) > cus) continue;
+        const int64_t n = (c->K + h - 1) / h;            // launches between checks, and the least halo for as many
+        f->R = 2;
+        f->TL = std::max(4, (int)((c->K + n - 1) / n));
+        const int tiles = panel_tiles(c, 2, f->TL);
+        if (tiles <= c->pcap) f->tiles = tiles;
+        return true;
+    }
     static const int shapes[7][2] = {{3, 6}, {4, 8}, {4, 7}, {6, 12}, {6, 10}, {8, 12}, {6, 8}};
     for (const auto& s : shapes) {
         if (c->efield_on && s[0] == 8) continue;
@@ -711,7 +732,7 @@ bool panel_shape(const slbm_ctx* c, Fuse* f)
     return true;
 }
 
-void launch_panel(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, const Fuse& f)
+void launch_panel(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, const Fuse& f, bool check)
 {
     PanelArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -730,7 +751,9 @@ void launch_panel(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, cons
     a.scale = s.scale;
     a.halo = f.TL;
     a.steps = steps;
-    a.tiles_x = (c->nx + 63 - 2 * f.TL) / (64 - 2 * f.TL);
+    a.tiles_x = (c->nx + panel_cols(f.R) - 1 - 2 * f.TL) / (panel_cols(f.R) - 2 * f.TL);
+    a.snap = s.snap;
+    a.partial = s.partial;
     a.code = s.code;
     a.bnodes = s.bnodes;
     a.E0 = s.E0;
@@ -742,7 +765,7 @@ void launch_panel(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, cons
         a.plan_n = c->pplan_n;
         a.tiles = c->ptiles;
     }
-    hipLaunchKernelGGL(panel_kernel(c->masked, c->efield_on, adjoint, f.R), dim3(wgs),
+    hipLaunchKernelGGL(panel_kernel(c->masked, c->efield_on, adjoint, f.R, check), dim3(wgs),
                        dim3(c->masked ? kPlateBlock : kPanelBlock), c->masked ? kPlateLds : 0, c->stream, a);
 }
 
@@ -1010,7 +1033,7 @@ int plan_fuse(slbm_ctx* c, Fuse* f)
 
 void launch_region(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, const Fuse& f, bool check = false)
 {
-    if (f.R > 0) launch_panel(c, adjoint, s, steps, f);
+    if (f.R > 0) launch_panel(c, adjoint, s, steps, f, check);
     else launch_tile(c, adjoint, s, steps, f.TL, check);
 }
 
@@ -1893,7 +1916,7 @@ int solid_lbm_init(const slbm_problem* p, slbm_ctx** out)
     c->stream = (hipStream_t)p->stream;
     c->E_cur = p->E;
     c->nblk = (N + kBlock - 1) / kBlock;
-    c->pcap = (2 * N + kBlock - 1) / kBlock + 2;
+    c->pcap = std::max<int64_t>((2 * N + kBlock - 1) / kBlock + 2, c->simds / 4);
 
     // Cbar (eq. node_J) on the host, over the observation set
     double cb = 0.0;

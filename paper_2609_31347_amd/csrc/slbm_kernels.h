@@ -1253,7 +1253,8 @@ __device__ __forceinline__ void tile_order(const TileArgs& a, int x0, int y0, in
     for (int j = 0; j < kTileNPT; ++j) ni[j] = order[threadIdx.x + j * kTileBlock];
 }
 
-// Sums (a, b) over a workgroup's kTileBlock threads into out[0], out[1] (thread 0 writes).
+// Sums (a, b) over a workgroup's BLOCK threads into out[0], out[1] (thread 0 writes).
+template <int BLOCK>
 __device__ __forceinline__ void block_sum2_tile(double a, double b, double* out)
 {
 #pragma unroll
@@ -1261,14 +1262,14 @@ __device__ __forceinline__ void block_sum2_tile(double a, double b, double* out)
         a += __shfl_xor(a, o);
         b += __shfl_xor(b, o);
     }
-    __shared__ double pa[kTileBlock / 64], pb[kTileBlock / 64];
+    __shared__ double pa[BLOCK / 64], pb[BLOCK / 64];
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     if (lane == 0) { pa[w] = a; pb[w] = b; }
     __syncthreads();
     if (threadIdx.x == 0) {
         double x = 0.0, y = 0.0;
 #pragma unroll
-        for (int i = 0; i < kTileBlock / 64; ++i) { x += pa[i]; y += pb[i]; }
+        for (int i = 0; i < BLOCK / 64; ++i) { x += pa[i]; y += pb[i]; }
         out[0] = x;
         out[1] = y;
     }
@@ -1524,7 +1525,7 @@ __device__ __forceinline__ void tile_body(const TileArgs& a, int tile, double* l
                 for (int q = 0; q < 8; ++q) stg(a.dst + q * N + n, out[j][q]);
             }
         }
-        if (CHECK && s == 1) block_sum2_tile(num, den, a.partial + 2 * (int64_t)tile);
+        if (CHECK && s == 1) block_sum2_tile<kTileBlock>(num, den, a.partial + 2 * (int64_t)tile);
         if (last) break;
         if (!MASKED) __syncthreads();               // in place: every pull read before the writes
 #pragma unroll
@@ -1989,7 +1990,7 @@ __device__ __forceinline__ void persist_nodes(const BatchInst& I, int par, int b
         }
 #undef BN_CASE
     }
-    if (check) block_sum2_tile(num, den, a.partial + 2 * (int64_t)blk);
+    if (check) block_sum2_tile<kTileBlock>(num, den, a.partial + 2 * (int64_t)blk);
 }
 
 // Residual test of an instance after its check step t: the sum of its nnb
@@ -2003,7 +2004,7 @@ __device__ __forceinline__ void persist_resid(const BatchInst& I, const PersistI
         b += partial[2 * k + 1];
     }
     __shared__ double out[2];
-    block_sum2_tile(a, b, out);
+    block_sum2_tile<kTileBlock>(a, b, out);
     if (threadIdx.x == 0) {
         Status* st = I.status;
         const double num = out[0], den = out[1];

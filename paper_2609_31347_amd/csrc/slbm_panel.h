@@ -15,6 +15,14 @@ namespace slbm {
 // `halo` nodes on every side is recomputed; the rest is written back after
 // `steps` <= halo sweeps.
 //
+// Panels of 32 columns (WC; R = 2) hold two row blocks per wave, one in each
+// half: their neighbours' rows come from LDS as between waves, and the lane
+// shifts that cross the halves bring values to the outermost columns only, which
+// are halo.  Their region, 32 x 32, is the LDS tiles' with a third of the LDS
+// accesses and no index arithmetic: a launch of 8 steps at 256^2 takes 8.6 us
+// against 10.3, of which about 3.4 are the launch and 2.4 the loads.  Their first
+// sweep may be a residual check (CHECK): the wave sums follow the last sweep.
+//
 // The arithmetic per node is the single-step kernels' own (collide_bulk,
 // adj_collide_bulk), so a launch of k sweeps equals k single sweeps bit for
 // bit.
@@ -61,6 +69,9 @@ struct PanelArgs {
     int64_t N;
     double k11, ks, kd, nu, scale;
     int32_t halo, steps, tiles_x;
+    // launches whose first sweep is a residual check: the state of the last check, sums by workgroup
+    double* __restrict__ snap;
+    double* __restrict__ partial;
     // plates
     const int32_t* __restrict__ code;
     const BNode* __restrict__ bnodes;
@@ -86,10 +97,10 @@ __device__ __forceinline__ int panel_slot(int e) { return (e % kPanelBWaves) * 6
 
 // The bulk waves of a tile.  MASKED: io holds 8 doubles per boundary slot,
 // cnt the boundary nodes per wave, nbt the tile's.
-template <bool MASKED, bool EFIELD, bool ADJ, int R>
+template <bool MASKED, bool EFIELD, bool ADJ, int R, int WC, bool CHECK = false>
 __device__ __forceinline__ void panel_tile(const PanelArgs& a, int tile, double* edge, double2* io, int* cnt, int nbt)
 {
-    constexpr int W = kPanelWaves;
+    constexpr int HW = 64 / WC, W = kPanelWaves * HW;    // row blocks per wave, in all
     // planes pulled from the row below (A: none, x - 1, x + 1) and above (B: none, x + 1, x - 1)
     constexpr int A0 = ADJ ? 3 : 1, A1 = ADJ ? 6 : 4, A2 = ADJ ? 7 : 5;
     constexpr int B0 = ADJ ? 1 : 3, B1 = ADJ ? 4 : 6, B2 = ADJ ? 5 : 7;
@@ -98,14 +109,17 @@ __device__ __forceinline__ void panel_tile(const PanelArgs& a, int tile, double*
     const int nx = a.nx, ny = a.ny, h = a.halo;
     const int64_t N = a.N;
     constexpr int RY = W * R;
-    const int x0 = (tile % a.tiles_x) * (64 - 2 * h) - h, y0 = (tile / a.tiles_x) * (RY - 2 * h) - h;
-    const int x = wrapi(x0 + lane, nx);
-    const bool colin = lane >= h && lane < 64 - h && x0 + lane < nx;   // columns this tile writes
+    const int x0 = (tile % a.tiles_x) * (WC - 2 * h) - h, y0 = (tile / a.tiles_x) * (RY - 2 * h) - h;
+    const int col = lane % WC, v = w * HW + lane / WC;   // column and row block of this lane
+    const int x = wrapi(x0 + col, nx);
+    const bool colin = col >= h && col < WC - h && x0 + col < nx;      // columns this tile writes
     double o[R][8], c0[R], c1[R], rk11[R], rks[R];
     int64_t cell[R];
     int cd[R], bs[R];
+    double s0[CHECK ? R : 1], s1[CHECK ? R : 1], num = 0.0, den = 0.0;
+    bool own[CHECK ? R : 1];
     {
-        int y = wrapi(y0 + w * R, ny);
+        int y = wrapi(y0 + v * R, ny);
 #pragma unroll
         for (int r = 0; r < R; ++r) {
             const int64_t n = (int64_t)y * nx + x;
@@ -116,17 +130,23 @@ __device__ __forceinline__ void panel_tile(const PanelArgs& a, int tile, double*
             c0[r] = ldg(a.g + n);
             c1[r] = ldg(a.g + N + n);
             if (EFIELD) rk11[r] = ldg(a.E + n);
+            if (CHECK) {
+                const int ry = v * R + r;
+                own[r] = colin && ry >= h && ry < RY - h && y0 + ry < ny;
+                s0[r] = own[r] ? ldg(a.snap + n) : 0.0;
+                s1[r] = own[r] ? ldg(a.snap + N + n) : 0.0;
+            }
             y = y + 1 == ny ? 0 : y + 1;
         }
     }
     auto publish = [&](int par) {
-        double* e = edge + (size_t)(par * W + w) * 6 * 64 + lane;
+        double* e = edge + (size_t)(par * W + v) * 6 * WC + col;
         e[0] = o[R - 1][A0];
-        e[64] = o[R - 1][A1];
-        e[128] = o[R - 1][A2];
-        e[192] = o[0][B0];
-        e[256] = o[0][B1];
-        e[320] = o[0][B2];
+        e[WC] = o[R - 1][A1];
+        e[2 * WC] = o[R - 1][A2];
+        e[3 * WC] = o[0][B0];
+        e[4 * WC] = o[0][B1];
+        e[5 * WC] = o[0][B2];
     };
     publish(0);
     uint32_t rowb = 0;                                   // rows with boundary nodes
@@ -143,7 +163,7 @@ __device__ __forceinline__ void panel_tile(const PanelArgs& a, int tile, double*
         if (lane == 0) cnt[w] = nbw;
         __syncthreads();
         int base = 0;
-        for (int v = 0; v < w; ++v) base += cnt[v];
+        for (int k = 0; k < w; ++k) base += cnt[k];
 #pragma unroll
         for (int r = 0; r < R; ++r) bs[r] = panel_slot(base + bs[r]);
     }
@@ -157,21 +177,21 @@ __device__ __forceinline__ void panel_tile(const PanelArgs& a, int tile, double*
             rks[r] = rl.ks;
         }
     }
-    const int lm = max(lane - 1, 0), lp = min(lane + 1, 63);
+    const int lm = max(col - 1, 0), lp = min(col + 1, WC - 1);
     for (int s = 1; s <= a.steps; ++s) {
         __syncthreads();
         const int m = h - (a.steps - s);                 // this sweep computes rows [m, RY - m)
-        if (w * R + R <= m || w * R >= RY - m) {
+        if ((w + 1) * HW * R <= m || w * HW * R >= RY - m) {
             if (MASKED && nbt) {
                 __syncthreads();
                 __syncthreads();
             }
             continue;
         }
-        const double* eb = edge + (size_t)(((s - 1) & 1) * W + max(w - 1, 0)) * 6 * 64;
-        const double* ea = edge + ((size_t)(((s - 1) & 1) * W + min(w + 1, W - 1)) * 6 + 3) * 64;
-        const double la[3] = {eb[lane], eb[64 + lm], eb[128 + lp]};
-        const double lb[3] = {ea[lane], ea[64 + lp], ea[128 + lm]};
+        const double* eb = edge + (size_t)(((s - 1) & 1) * W + max(v - 1, 0)) * 6 * WC;
+        const double* ea = edge + ((size_t)(((s - 1) & 1) * W + min(v + 1, W - 1)) * 6 + 3) * WC;
+        const double la[3] = {eb[col], eb[WC + lm], eb[2 * WC + lp]};
+        const double lb[3] = {ea[col], ea[WC + lp], ea[2 * WC + lm]};
         auto row = [&](int r, const double (&A)[3], const double (&B)[3]) {
             double f[8];
             f[0] = ADJ ? lane_down(o[r][0]) : lane_up(o[r][0]);
@@ -189,11 +209,18 @@ __device__ __forceinline__ void panel_tile(const PanelArgs& a, int tile, double*
                 }
             }
             const double k11 = EFIELD ? rk11[r] : a.k11, ks = EFIELD ? rks[r] : a.ks, kd = EFIELD ? rk11[r] : a.kd;
-            if (!ADJ) {
-                double d0, d1;
-                collide_bulk(f, c0[r], c1[r], k11, ks, kd, d0, d1);
-            } else {
-                adj_collide_bulk(f, c0[r], c1[r], k11, ks, kd);
+            double d0, d1;
+            if (CHECK && ADJ) {
+                d0 = (f[0] - f[2]) + (f[4] - f[5]) + (f[7] - f[6]);
+                d1 = (f[1] - f[3]) + (f[4] + f[5]) - (f[6] + f[7]);
+            }
+            if (!ADJ) collide_bulk(f, c0[r], c1[r], k11, ks, kd, d0, d1);
+            else adj_collide_bulk(f, c0[r], c1[r], k11, ks, kd);
+            if (CHECK && s == 1 && own[r]) {
+                num += (d0 - s0[r]) * (d0 - s0[r]) + (d1 - s1[r]) * (d1 - s1[r]);
+                den += d0 * d0 + d1 * d1;
+                stg(a.snap + cell[r], d0);
+                stg(a.snap + N + cell[r], d1);
             }
 #pragma unroll
             for (int q = 0; q < 8; ++q) o[r][q] = f[q];
@@ -247,10 +274,11 @@ __device__ __forceinline__ void panel_tile(const PanelArgs& a, int tile, double*
         }
         if (s < a.steps) publish(s & 1);
     }
+    if (CHECK) block_sum2_tile<kPanelBlock>(num, den, a.partial + 2 * (int64_t)tile);
     if (!colin) return;
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int ry = w * R + r;
+        const int ry = v * R + r;
         if (ry < h || ry >= RY - h || y0 + ry >= ny) continue;
         if (MASKED && cd[r] < 0) continue;
 #pragma unroll
@@ -335,12 +363,12 @@ __device__ __forceinline__ void panel_boundary(const PanelArgs& a, int wg, int b
     }
 }
 
-template <bool EFIELD, bool ADJ, int R>
+template <bool EFIELD, bool ADJ, int R, int WC, bool CHECK>
 __global__ __launch_bounds__(kPanelBlock) void k_sweep_panel(PanelArgs a)
 {
     if (a.status->stop) return;
     __shared__ __align__(16) double edge[kPanelEdge];
-    panel_tile<false, EFIELD, ADJ, R>(a, xcd_order(blockIdx.x, gridDim.x), edge, nullptr, nullptr, 0);
+    panel_tile<false, EFIELD, ADJ, R, WC, CHECK>(a, xcd_order(blockIdx.x, gridDim.x), edge, nullptr, nullptr, 0);
 }
 
 template <bool EFIELD, bool ADJ, int R>
@@ -354,7 +382,7 @@ __global__ __launch_bounds__(kPlateBlock) void k_sweep_plate(PanelArgs a)
     const int tile = a.tiles[wg];
     const int nbt = a.plan_n[wg];
     double2* io = reinterpret_cast<double2*>(lds + kPanelEdge);
-    if (w < kPanelWaves) panel_tile<true, EFIELD, ADJ, R>(a, tile, lds, io, cnt, nbt);
+    if (w < kPanelWaves) panel_tile<true, EFIELD, ADJ, R, 64>(a, tile, lds, io, cnt, nbt);
     else if (nbt) panel_boundary<EFIELD, ADJ>(a, wg, w - kPanelWaves, io, nbt);
 }
 

@@ -1,0 +1,73 @@
+"""Register panels of 32 columns (needs a GPU): launches of several steps equal
+single sweeps bit for bit, and a solve whose checks are the first sweeps of
+such launches stops where single steps stop, with the same outputs."""
+import numpy as np
+import pytest
+
+from paper_2609_31347_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+# halo (GPU of 256 compute units) 14 with several wrapped copies of the grid, 14, 12, 11 with ragged panels,
+# 8 on one round of whole panels, 6; the first size past them; a strip of a few columns
+SIZES = ((5, 3), (33, 61), (128, 128), (157, 149), (256, 256), (300, 300), (321, 320), (3, 2000))
+
+
+def problem(S, nx, ny, efield, **more):
+    dx = 1.0 / max(nx, ny)
+    rng = np.random.default_rng(nx + ny)
+    F = 1e-2 * rng.standard_normal((2, ny, nx))
+    p = dict(nx=nx, ny=ny, dx=dx, E=1.0, nu=0.3, domain=0, target=1e-3 * F[::-1].copy(), **more)
+    if not efield:
+        p.update(control_kind=S.CTRL_FORCE_NODAL)
+        return p, F
+    p.update(control_kind=S.CTRL_E_NODAL, fixed_force=F)
+    return p, 1.0 + 0.3 * np.tanh(rng.standard_normal((ny, nx)))
+
+
+@pytest.mark.parametrize("efield", [False, True])
+@pytest.mark.parametrize("nx,ny", SIZES)
+def test_panels_equal_single_steps_bit_for_bit(nx, ny, efield):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_31347_amd import slbm as S
+    p, control = problem(S, nx, ny, efield, tol=0.0, max_steps=14)
+
+    def fields(tuning):
+        ctx = S.solid_lbm_init(p)
+        S.solid_lbm_set_tuning(ctx, tuning, 0)
+        S.solid_lbm_set_control(ctx, control)
+        S.solid_lbm_run_steps(ctx, 37)
+        pops = S.solid_lbm_get_field(ctx, S.FIELD_POPS)
+        S.primal_solve(ctx, control)
+        S.solid_lbm_run_adjoint_steps(ctx, 29)
+        return pops, S.solid_lbm_get_field(ctx, S.FIELD_ADJ_POPS)
+    ref, got = fields(1), fields(-1)
+    assert np.abs(ref[0]).max() > 0 and np.abs(ref[1]).max() > 0
+    assert np.array_equal(ref[0], got[0])
+    assert np.array_equal(ref[1], got[1])
+
+
+@pytest.mark.parametrize("efield", [False, True])
+@pytest.mark.parametrize("K", [5, 14, 20, 33])       # one short launch, one whole, two, three
+def test_checks_in_panels_stop_where_single_steps_do(K, efield):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_31347_amd import slbm as S
+    p, control = problem(S, 61, 47, efield, tol=1e-4, max_steps=20000, check_interval=K)
+    out = []
+    for tuning in (1, -1):
+        ctx = S.solid_lbm_init(p)
+        S.solid_lbm_set_tuning(ctx, tuning, 0)
+        rc, J, g, pi, ai = S.objective_and_grad(ctx, control)
+        out.append((rc, J, pi.steps, ai.steps, np.asarray(g), S.solid_lbm_get_field(ctx, S.FIELD_ADJ_POPS),
+                    pi.residual, ai.residual))
+    a, b = out
+    # the fixed force of the modulus problem has a mean, which no steady state balances: it runs to max_steps
+    assert a[0] == b[0] == (1 if efield else 0)
+    assert a[1:4] == b[1:4]
+    assert np.array_equal(a[4], b[4]) and np.array_equal(a[5], b[5])
+    for k in (6, 7):                                 # sums over panels instead of blocks
+        assert abs(a[k] - b[k]) <= 1e-9 * abs(a[k])
