@@ -643,8 +643,9 @@ template <bool E, bool A>
 panel_fn plate_of(int R)
 {
     switch (R) {
-        case 3: return k_sweep_plate<E, A, 3>;
-        default: return k_sweep_plate<E, A, 4>;
+        case 2: return k_sweep_plate<E, A, 2, 32>;
+        case 3: return k_sweep_plate<E, A, 3, 64>;
+        default: return k_sweep_plate<E, A, 4, 64>;
     }
 }
 panel_fn panel_kernel(bool masked, bool efield, bool adjoint, int R, bool check = false)
@@ -779,7 +780,7 @@ struct PlateTiles {
 
 PlateTiles plate_tiles(const slbm_ctx* c, int R, int h)
 {
-    const int tw = 64 - 2 * h, th = kPanelWaves * R - 2 * h;
+    const int cols = panel_cols(R), rows = kPanelWaves * (64 / cols) * R, tw = cols - 2 * h, th = rows - 2 * h;
     const int tx = (c->nx + tw - 1) / tw, ty = (c->ny + th - 1) / th;
     // tiles whose region holds coordinate v, periodic copies one by one
     auto spans = [](int v, int n, int t, int size, int h, int tiles, std::vector<int>& out) {
@@ -792,8 +793,8 @@ PlateTiles plate_tiles(const slbm_ctx* c, int R, int h)
     PlateTiles out;
     int row = -1;
     for (int32_t n : c->bcells) {                        // in row-major order
-        if (n / c->nx != row) spans(row = n / c->nx, c->ny, th, kPanelWaves * R, h, ty, by);
-        spans(n % c->nx, c->nx, tw, 64, h, tx, bx);
+        if (n / c->nx != row) spans(row = n / c->nx, c->ny, th, rows, h, ty, by);
+        spans(n % c->nx, c->nx, tw, cols, h, tx, bx);
         for (int j : by)
             for (int i : bx) out.most = std::max(out.most, ++count[(size_t)j * tx + i]);
     }
@@ -841,16 +842,18 @@ double plate_launch_us(int rims, int inners, int m, double tr, double ti)
 
 // Automatic panel shape of a plate (found once per context: it depends on the
 // geometry only).  Plates whose 16 x 16 LDS tiles fit the compute units in one
-// round keep those (250 x 150: 2.04 us per primal step against 2.2 for the best
-// panels).  Beyond, the shape of least time by plate_launch_us, with tile times
-// fitted to E-field plates from 64 x 39 to 1000 x 600 (us): with boundary nodes
-// 8 + 1.53 h and 12.3 + 1.73 h for R = 3 and 4 rows per lane, without 5 + 0.7 h
-// and 6.5 + 0.91 h.  It takes the fastest of the shapes at every size measured
-// (us per primal step, fastest and slowest of the five): 384 x 231 (3, 8) 2.57
-// - 3.56, 512 x 308 (3, 8) 2.65 - 3.73, 700 x 420 (4, 8) 3.42 - 4.57, 850 x 510
-// (4, 6) 4.29 - 5.69, 1000 x 600 (4, 6) 5.81 - 7.64.  R = 2 is slower
-// throughout.  A region must not hold more boundary nodes than the boundary
-// waves have lanes; plates with denser rims keep the LDS tiles.
+// round keep those (mean of primal and adjoint, us per step: 250 x 150 1.85
+// against 1.91 for the best panels, of 32 columns and 11 steps; 64 x 39 1.70
+// against 1.67 with 14 steps, more than its check interval holds).  Beyond, the
+// shape of least time by plate_launch_us, with tile times fitted to E-field
+// plates from 64 x 39 to 1000 x 600 (us): with boundary nodes 10.5 + 0.92 h, 8 +
+// 1.53 h and 12.3 + 1.73 h for R = 2 (32 columns), 3 and 4 rows per lane, without
+// 5 + 0.4 h, 5 + 0.7 h and 6.5 + 0.91 h.  It takes the fastest of the shapes at
+// every size measured (us per primal step): 340 x 204 to 420 x 252 (2, 8) 2.3
+// against 2.6 - 2.7 with (3, 8), 450 x 270 (3, 8) 2.69, 512 x 308 (3, 8) 2.65 -
+// 3.73, 700 x 420 (4, 8) 3.42 - 4.57, 850 x 510 (4, 6) 4.29 - 5.69, 1000 x 600
+// (4, 6) 5.81 - 7.64.  A region must not hold more boundary nodes than the
+// boundary waves have lanes; plates with denser rims keep the LDS tiles.
 bool plate_shape(slbm_ctx* c, Fuse* f)
 {
     if (c->tb_T >= 0 || c->tile_w > 0) return false;
@@ -858,14 +861,14 @@ bool plate_shape(slbm_ctx* c, Fuse* f)
     if (c->pshape[0] < 0) {
         c->pshape[0] = 0;
         if ((int64_t)((c->nx + 15) / 16) * ((c->ny + 15) / 16) > cus) {
-            static const int shapes[5][2] = {{3, 6}, {3, 8}, {4, 6}, {4, 8}, {4, 10}};
+            static const int shapes[6][2] = {{2, 8}, {3, 6}, {3, 8}, {4, 6}, {4, 8}, {4, 10}};
             double best = INFINITY;
             for (const auto& s : shapes) {
                 const int R = s[0], h = s[1];
                 PlateTiles t = plate_tiles(c, R, h);
                 if (t.list.empty() || t.most > kPanelCap) continue;
-                const double tr = R == 3 ? 8.0 + 1.53 * h : 12.3 + 1.73 * h;
-                const double ti = R == 3 ? 5.0 + 0.7 * h : 6.5 + 0.91 * h;
+                const double tr = R == 2 ? 10.5 + 0.92 * h : R == 3 ? 8.0 + 1.53 * h : 12.3 + 1.73 * h;
+                const double ti = R == 2 ? 5.0 + 0.4 * h : R == 3 ? 5.0 + 0.7 * h : 6.5 + 0.91 * h;
                 const int inner = (int)t.list.size() - t.rim;
                 const double us = plate_launch_us((t.rim + kXcds - 1) / kXcds, (inner + kXcds - 1) / kXcds,
                                                   (int)std::max<int64_t>(1, cus / kXcds), tr, ti) / h;
@@ -918,8 +921,8 @@ int build_panel_plan(slbm_ctx* c, int R, int h)
     a.nx = c->nx;
     a.ny = c->ny;
     a.halo = h;
-    a.tiles_x = (c->nx + 63 - 2 * h) / (64 - 2 * h);
-    hipLaunchKernelGGL(k_panel_plan, dim3((unsigned)wgs), dim3(kPanelBlock), 0, c->stream, a, R, plan, coef, count);
+    a.tiles_x = (c->nx + panel_cols(R) - 1 - 2 * h) / (panel_cols(R) - 2 * h);
+    hipLaunchKernelGGL(k_panel_plan, dim3((unsigned)wgs), dim3(kPanelBlock), 0, c->stream, a, R, panel_cols(R), plan, coef, count);
     HIPCHK(c, hipGetLastError());
     HIPCHK(c, hipStreamSynchronize(c->stream));      // plive is read by the copy
     c->pplan = plan;

@@ -371,7 +371,7 @@ __global__ __launch_bounds__(kPanelBlock) void k_sweep_panel(PanelArgs a)
     panel_tile<false, EFIELD, ADJ, R, WC, CHECK>(a, xcd_order(blockIdx.x, gridDim.x), edge, nullptr, nullptr, 0);
 }
 
-template <bool EFIELD, bool ADJ, int R>
+template <bool EFIELD, bool ADJ, int R, int WC>
 __global__ __launch_bounds__(kPlateBlock) void k_sweep_plate(PanelArgs a)
 {
     if (a.status->stop) return;
@@ -382,7 +382,7 @@ __global__ __launch_bounds__(kPlateBlock) void k_sweep_plate(PanelArgs a)
     const int tile = a.tiles[wg];
     const int nbt = a.plan_n[wg];
     double2* io = reinterpret_cast<double2*>(lds + kPanelEdge);
-    if (w < kPanelWaves) panel_tile<true, EFIELD, ADJ, R, 64>(a, tile, lds, io, cnt, nbt);
+    if (w < kPanelWaves) panel_tile<true, EFIELD, ADJ, R, WC>(a, tile, lds, io, cnt, nbt);
     else if (nbt) panel_boundary<EFIELD, ADJ>(a, wg, w - kPanelWaves, io, nbt);
 }
 
@@ -390,16 +390,17 @@ __global__ __launch_bounds__(kPlateBlock) void k_sweep_plate(PanelArgs a)
 // order of the tile list): the boundary nodes of its region in region order,
 // spread over the boundary waves, with their records in planes, so that a
 // boundary wave loads consecutive words.
-__global__ __launch_bounds__(kPanelBlock) void k_panel_plan(PanelArgs a, int R, int2* plan, double* coef, int32_t* plan_n)
+__global__ __launch_bounds__(kPanelBlock) void k_panel_plan(PanelArgs a, int R, int cols, int2* plan, double* coef, int32_t* plan_n)
 {
     const int wg = blockIdx.x, tile = a.tiles[wg], lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int h = a.halo, RY = kPanelWaves * R;
-    const int x0 = (tile % a.tiles_x) * (64 - 2 * h) - h, y0 = (tile / a.tiles_x) * (RY - 2 * h) - h;
-    const int x = wrapi(x0 + lane, a.nx);
-    const bool colin = lane >= h && lane < 64 - h && x0 + lane < a.nx;
+    const int h = a.halo, HW = 64 / cols, RY = kPanelWaves * HW * R;
+    const int x0 = (tile % a.tiles_x) * (cols - 2 * h) - h, y0 = (tile / a.tiles_x) * (RY - 2 * h) - h;
+    const int col = lane % cols, row0 = (w * HW + lane / cols) * R;
+    const int x = wrapi(x0 + col, a.nx);
+    const bool colin = col >= h && col < cols - h && x0 + col < a.nx;
     __shared__ int cnt[kPanelWaves];
     int mine = 0;
-    for (int r = 0; r < R; ++r) mine += __popcll(__ballot(a.code[(int64_t)wrapi(y0 + w * R + r, a.ny) * a.nx + x] > 0));
+    for (int r = 0; r < R; ++r) mine += __popcll(__ballot(a.code[(int64_t)wrapi(y0 + row0 + r, a.ny) * a.nx + x] > 0));
     if (lane == 0) cnt[w] = mine;
     __syncthreads();
     int at = 0, total = 0;
@@ -408,7 +409,7 @@ __global__ __launch_bounds__(kPanelBlock) void k_panel_plan(PanelArgs a, int R, 
         total += cnt[v];
     }
     for (int r = 0; r < R; ++r) {
-        const int ry = w * R + r;
+        const int ry = row0 + r;
         const int64_t n = (int64_t)wrapi(y0 + ry, a.ny) * a.nx + x;
         const int code = a.code[n];
         const uint64_t b = __ballot(code > 0);

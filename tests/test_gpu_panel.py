@@ -62,7 +62,7 @@ def perforated(nx, ny, pitch):
     return dict(nx=nx, ny=ny, dx=dx, active=active, bc=bc, wall=wall, normal=nrm)
 
 
-# (3, 8), (4, 8) and (4, 6) in one and several rounds by size; the paper's plate with two holes; a
+# (2, 8), (3, 8), (4, 8) and (4, 6) in one and several rounds by size; the paper's plate with two holes; a
 # perforated plate of up to 256 boundary nodes a region, and one beyond (LDS tiles)
 @pytest.mark.parametrize("what,size,efield", [("clamped", 384, False), ("clamped", 385, True), ("clamped", 512, True),
                                               ("clamped", 560, False), ("clamped", 701, True), ("clamped", 900, False),

@@ -1,6 +1,7 @@
 """Register panels of 32 columns (needs a GPU): launches of several steps equal
-single sweeps bit for bit, and a solve whose checks are the first sweeps of
-such launches stops where single steps stop, with the same outputs."""
+single sweeps bit for bit, on periodic grids and on plates, and a solve whose
+checks are the first sweeps of such launches stops where single steps stop,
+with the same outputs."""
 import numpy as np
 import pytest
 
@@ -71,3 +72,30 @@ def test_checks_in_panels_stop_where_single_steps_do(K, efield):
     assert np.array_equal(a[4], b[4]) and np.array_equal(a[5], b[5])
     for k in (6, 7):                                 # sums over panels instead of blocks
         assert abs(a[k] - b[k]) <= 1e-9 * abs(a[k])
+
+
+# the smallest and largest clamped plate that take them on a GPU of 256 compute units, and one between
+@pytest.mark.parametrize("size,efield", [(336, True), (371, False), (420, True)])
+def test_plate_panels_equal_single_steps_bit_for_bit(size, efield):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_31347_amd import slbm as S
+    cp = I.clamped_plate(size, int(np.ceil(0.6 * size)))
+    ny, nx = cp["active"].shape
+    p, control = problem(S, nx, ny, efield, tol=0.0, max_steps=14)
+    p.update(dx=cp["dx"], domain=S.MASKED, node_mask=cp["active"].astype(np.uint8), link_bc=cp["bc"],
+             link_wall=cp["wall"], link_normal=cp["normal"])
+    out = []
+    for tuning in (1, -1):
+        ctx = S.solid_lbm_init(p)
+        S.solid_lbm_set_tuning(ctx, tuning, 0)
+        S.solid_lbm_set_control(ctx, control)
+        S.solid_lbm_run_steps(ctx, 37)
+        pops = S.solid_lbm_get_field(ctx, S.FIELD_POPS)
+        S.primal_solve(ctx, control)
+        S.solid_lbm_run_adjoint_steps(ctx, 29)
+        out.append((pops, S.solid_lbm_get_field(ctx, S.FIELD_ADJ_POPS)))
+    assert np.abs(out[0][0]).max() > 0 and np.abs(out[0][1]).max() > 0
+    assert np.array_equal(out[0][0], out[1][0])
+    assert np.array_equal(out[0][1], out[1][1])
