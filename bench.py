@@ -33,12 +33,13 @@ sys.path.insert(0, ROOT)
 
 BYTES_PER_NODE = 144.0      # 8 pops read + 8 written (8 B each) + 2 forcing / residual reads
 PEAK_GBS = 8000.0           # MI355X HBM3E
-# Measured HBM bytes per launch of the dominant kernel, keyed by (N, T, H):
+# Measured HBM bytes per launch of the dominant kernel, keyed by (N, T, H), T the
+# steps per launch (the automatic shape's too, with H 0):
 # rocprofv3 FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 (the factors the benchmark's
 # plain copy of one population buffer reads in the same runs), mean per
 # dispatch of the fused primal sweep, with the hash of the kernel code they
-# were taken with (kernel_source_hash; profiles/k_sweep_tb_periodic_2048_bench.md).
-TRAFFIC = {(2048, 8, 96): {"bytes": (2.0 * 198522.7 + 271613.1) * 1024, "sources": "bf581a3a5fc7624e"}}
+# were taken with (kernel_source_hash; profiles/k_sweep_pipe_periodic_2048_bench.md).
+TRAFFIC = {(2048, 16, 0): {"bytes": (2.0 * 201735.0 + 262144.0) * 1024, "sources": "6d3939dcd6e15c82"}}
 
 
 def parse():
@@ -597,7 +598,7 @@ def kernel_source_hash():
     figures taken with other code do not describe the running kernel."""
     import hashlib
     h = hashlib.sha256()
-    for f in ("slbm_kernels.h", "slbm_device.h"):
+    for f in ("slbm_kernels.h", "slbm_device.h", "slbm_panel.h", "slbm_pipe.h"):
         with open(os.path.join(ROOT, "paper_2609_31347_amd", "csrc", f), encoding="utf-8") as fh:
             h.update(code_text(fh.read()).encode())
     return h.hexdigest()[:16]
@@ -710,6 +711,8 @@ def main():
     tw, th = tune.get("tiles", [0, 0])
     if tw > 0:
         kname = f"k_sweep_tile<false,false,false> (primal sweep, {T} time steps per launch, {tw}x{th} tiles in LDS)"
+    elif T < 0:
+        kname = None                                       # named by its steps per launch below
     elif T > 1:
         kname = f"k_sweep_tb<{T},false> (primal sweep, {T} time steps per launch, {H} rows per wave)"
     else:
@@ -719,12 +722,17 @@ def main():
     if lp == 0:
         raise RuntimeError("no fused launches were timed")
     steps_per_launch = sp / lp
+    if kname is None and steps_per_launch > 15:
+        kname = (f"k_sweep_pipe<2,8,false,{'true' if n % 2 == 0 else 'false'}> (primal sweep, 16 time steps per "
+                 f"launch over 8 waves; wave strips before a check)")
+    elif kname is None:
+        kname = "automatic shape (register panels or LDS tiles)"
     bytes_launch = BYTES_PER_NODE * cells                  # fused-launch minimum: pops in + out, forcing in, once
     us_p = msp / lp * 1e3
     us_a = msa / la * 1e3 if la else float("nan")
     ach = bytes_launch / (us_p * 1e-6) / 1e9
     src_hash = kernel_source_hash()
-    entry = TRAFFIC.get((n, T, H))
+    entry = TRAFFIC.get((n, T if T > 0 else int(round(steps_per_launch)), H))
     traffic, tnote = None, None
     if entry is None:
         tnote = f"no counter record for grid {n}, T {T}, H {H}"
@@ -768,7 +776,8 @@ def main():
                              "once and written once, its 2 forcing values read once: 144 B per node per launch) "
                              "/ the launch's average duration from HIP events on the library stream over the "
                              "timed steps; traffic = HBM bytes per launch from rocprofv3 FETCH_SIZE / WRITE_SIZE "
-                             "scaled by a plain copy's factors"},
+                             "scaled by a plain copy's factors; launches of 16 steps are bound by FP64 issue at "
+                             "the clock that their power leaves, not by HBM"},
         "tuning": {"T": T, "H": H, "tiles": [tw, th], "cached": tune["cached"], "candidates_us": tune.get("us")},
     }
     if tnote:
