@@ -417,7 +417,7 @@ void launch_fused(slbm_ctx* c, bool adjoint, const SweepArgs& s, int T)
 // 240 tiles, 3.0 us).  Grids of one 8 x 8 tile per compute unit that check every
 // 9 to 12 steps take the whole interval in one launch, whose first sweep is the
 // check (8 steps and the rest as a second launch: the 64 x 39 plate, K = 10,
-// 2.80 us per step against 2.44).
+// 2.80 us per step against 2.44, 2.05 with the check in the launch).
 int tile_halo(const slbm_ctx* c)
 {
     if (c->tb_T >= 0) return std::max(1, std::min(c->tb_T, 8));
@@ -1919,6 +1919,8 @@ int solid_lbm_init(const slbm_problem* p, slbm_ctx** out)
     c->stream = (hipStream_t)p->stream;
     c->E_cur = p->E;
     c->nblk = (N + kBlock - 1) / kBlock;
+    // at least one sum per compute unit: a fused check hands in one per tile (64 x
+    // 39: 40 tiles, 21 blocks)
     c->pcap = std::max<int64_t>((2 * N + kBlock - 1) / kBlock + 2, c->simds / 4);
 
     // Cbar (eq. node_J) on the host, over the observation set

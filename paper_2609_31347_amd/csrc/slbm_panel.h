@@ -36,8 +36,8 @@ namespace slbm {
 // so on grids of more nodes than 16 x 16 tiles can cover in one round of
 // workgroups the panels win.  us per primal step, before (strips or two rounds
 // of tiles) / panel: 300^2 2.24 / 1.57, 371^2 2.60 / 1.65, 501 x 333 2.64 /
-// 1.78, 448^2 2.76 / 1.88, 512^2 2.87 / 2.18, 600^2 3.27 / 2.47, 700^2 3.62 /
-// 3.23; 800^2 4.14 / 4.25 (no gain: strips stay).
+// 1.78, 448^2 2.76 / 1.88, 512^2 2.87 / 2.18, 600^2 3.27 / 2.47; from 700^2 the
+// wave pipeline is faster (3.21 against 3.37).
 //
 // Plates (k_sweep_plate): four more waves run the boundary nodes, one per lane
 // with its record, closure values and relaxation in registers.  In a sweep the
