@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "solid_lbm_net.h"
 
@@ -288,18 +289,26 @@ __global__ __launch_bounds__(1024) void k_conv_bwd_w_split(const float* __restri
             zs[p * kBwdRow + co] = in ? dz[((int64_t)b * Cout + co) * HW + yy * W + xx] : 0.0f;
         }
         __syncthreads();
-        for (int j = part * per; j < (part + 1) * per; j += 8) {    // 8 pairs of one row of the tile
-            const int p = 2 * j + half;
-            const float* za = zs + p * kBwdRow + row;
-            const uint16_t* xa = xs + ((p / kTileX) * rw + p % kTileX) * ph + xoff;
+        // pixels outside the image have no part, not even that of a zero dz: their taps reach back into the image,
+        // and an Inf or NaN there times zero would be a NaN
+        const int cols = W - tx * kTileX, end = min((part + 1) * per, (H - ty * kTileY) * (kTileX / 2));
+        auto pairs = [&](auto ragged) {
+            for (int j = part * per; j < end; j += 8) {             // 8 pairs of one row of the tile
+                const int p = 2 * j + half, left = cols - p % kTileX;
+                if (decltype(ragged)::value && 2 * j % kTileX >= cols) continue;
+                const float* za = zs + p * kBwdRow + row;
+                const uint16_t* xa = xs + ((p / kTileX) * rw + p % kTileX) * ph + xoff;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const float av = za[2 * u * kBwdRow];
-                const float bv = bf2f(xa[2 * u * ph]);
-                s += av;
-                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc, 0, 0, 0);
+                for (int u = 0; u < 8; ++u) {
+                    const float av = za[2 * u * kBwdRow];
+                    const float bv = !decltype(ragged)::value || 2 * u < left ? bf2f(xa[2 * u * ph]) : 0.0f;
+                    s += av;
+                    acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av, bv, acc, 0, 0, 0);
+                }
             }
-        }
+        };
+        if (cols >= kTileX) pairs(std::false_type());
+        else pairs(std::true_type());
     }
     // [split][co][column], then one more column: the sums of dz
     float* out = ws + (size_t)(blockIdx.x * parts + part) * (nb * 32 + 1) * 32;
