@@ -417,13 +417,14 @@ void launch_fused(slbm_ctx* c, bool adjoint, const SweepArgs& s, int T)
 // 240 tiles, 3.0 us).  Grids of one 8 x 8 tile per compute unit that check every
 // 9 to 12 steps take the whole interval in one launch, whose first sweep is the
 // check (8 steps and the rest as a second launch: the 64 x 39 plate, K = 10,
-// 2.80 us per step against 2.44, 2.05 with the check in the launch).
-int tile_halo(const slbm_ctx* c)
+// 2.80 us per step against 2.44, 2.05 with the check in the launch).  Tiles set
+// by the caller keep 8 steps: a wider halo would not hold 16 x 16 of them.
+int tile_halo(const slbm_ctx* c, bool own_tile)
 {
     if (c->tb_T >= 0) return std::max(1, std::min(c->tb_T, 8));
     if (c->N <= 131072) {
         const int64_t t8 = (int64_t)((c->nx + 7) / 8) * ((c->ny + 7) / 8);
-        return c->tol > 0.0 && c->K > 8 && c->K <= 12 && t8 <= c->simds / 4 ? (int)c->K : 8;
+        return !own_tile && c->tol > 0.0 && c->K > 8 && c->K <= 12 && t8 <= c->simds / 4 ? (int)c->K : 8;
     }
     const int64_t cus = c->simds / 4;
     for (int h : {6, 5, 4, 3}) {
@@ -433,7 +434,7 @@ int tile_halo(const slbm_ctx* c)
     return 6;
 }
 
-int tile_steps(const slbm_ctx* c) { return use_tiles(c) ? tile_halo(c) : 1; }
+int tile_steps(const slbm_ctx* c) { return use_tiles(c) ? tile_halo(c, c->tile_w > 0) : 1; }
 
 // Interior tile of the LDS-tiled sweeps for a halo h: the region (tw + 2h) x
 // (th + 2h) must hold at most kTileMaxNodes nodes.  Automatic: a 32 x 32
@@ -2342,7 +2343,7 @@ int solid_lbm_set_tiles(slbm_ctx* c, int32_t tile_w, int32_t tile_h)
     if ((tile_w == 0) != (tile_h == 0) || tile_w < 0 || tile_h < 0)
         return fail(c, SLBM_EINVAL, "tile_w and tile_h must both be 0 (automatic) or both >= 1");
     if (tile_w > 0) {
-        const int h = tile_halo(c);
+        const int h = tile_halo(c, true);
         if ((tile_w + 2 * h) * (tile_h + 2 * h) > kTileMaxNodes)
             return fail(c, SLBM_EINVAL, "tile plus halo exceeds " + std::to_string(kTileMaxNodes) + " nodes");
     }
