@@ -707,6 +707,7 @@ int panel_tiles(const slbm_ctx* c, int R, int h)
 bool panel_shape(const slbm_ctx* c, Fuse* f)
 {
     if (c->masked || c->tb_T >= 0 || c->tile_w > 0) return false;
+    if (c->tb_H > 0 && !use_tiles(c)) return false;          // rows set by the caller: wave strips
     const int cus = c->simds / 4;
     f->T = 1;
     for (int h = 14; h >= 6; --h) {
