@@ -425,10 +425,12 @@ int solid_lbm_batch_set_persistent(slbm_batch *batch, int32_t on, int32_t rounds
  * context: fn(user, phase, step, residual) is called on the calling thread
  * from inside the batch solves when a check has been read back and at least
  * every_s seconds have passed since the last report; phase 0 = primal,
- * 1 = adjoint.  Host-driven launches report the time step of the check
- * read back and the largest residual among the instances still running then
- * that have completed a check (no report before the first such check; checks are read one behind, so that step can pass the last instance's
- * final step by up to two check intervals); persistent
+ * 1 = adjoint.  Host-driven launches report, of the instances still running
+ * that have completed a check (no report before the first such check), the
+ * largest residual and the smallest step of their latest checks read back:
+ * each instance keeps its own step counter, and all of them have reached that
+ * step.  Steps do not decrease within a half; checks are read up to two polls
+ * behind, so a report can follow an instance's final step; persistent
  * launches report the rounds run and residual -1 (not read back).  fn = NULL
  * turns reports off.  The callback must not call into the library with the
  * same batch. */

@@ -2913,10 +2913,9 @@ struct BatchClass {
         checked = false;
         return SLBM_OK;
     }
-    // reads the oldest pending poll (wait: block until it is there); false if none was read
+    // reads the oldest pending poll (wait: block until it is there); sets *got if one was read
     int read(bool wait, bool* got)
     {
-        *got = false;
         if (pending.empty()) return SLBM_OK;
         const int k = pending.front();
         if (wait) {
@@ -2992,12 +2991,15 @@ int batch_loop(slbm_batch* b, bool adjoint, std::vector<int64_t>& t_out, std::ve
                     break;
                 }
         if (got && b->progress) {
-            double worst = -1.0;       // of the running instances with a completed check
-            int64_t t = -1;
-            for (int i = 0; i < B; ++i) {
-                if (active[i] && b->seen_t[i] >= 0) worst = std::max(worst, b->seen_res[i]);
-                t = std::max(t, b->seen_t[i]);
-            }
+            // of the running instances with a completed check: the largest residual, and the step that all of
+            // them have reached (an instance's first check can lie before the step last reported: no report then)
+            double worst = -1.0;
+            int64_t t = INT64_MAX;
+            for (int i = 0; i < B; ++i)
+                if (active[i] && b->seen_t[i] >= 0) {
+                    worst = std::max(worst, b->seen_res[i]);
+                    t = std::min(t, b->seen_t[i]);
+                }
             auto now = std::chrono::steady_clock::now();
             if (worst >= 0.0 && t >= reported &&
                 std::chrono::duration<double>(now - last_report).count() >= b->progress_every) {
