@@ -1184,6 +1184,7 @@ int tangent_loop(slbm_ctx* c, const TangentArgs& base, int64_t* t_out, int* x_ou
     const int64_t K = c->K, last = c->max_steps;
     TangentArgs a = base;
     TangentTile tile = tangent_tile(c);
+    const bool fuse = c->tb_T < 0 || c->tb_T > 1;    // solid_lbm_set_tuning(ctx, 1, 0): one step per launch
     int cur = 0, last_in = 0;
     int64_t chunk = 0;
     int64_t s = 0;
@@ -1204,7 +1205,7 @@ int tangent_loop(slbm_ctx* c, const TangentArgs& base, int64_t* t_out, int* x_ou
             a.dstd = c->td[cur ^ 1];
             int64_t plain = std::min(end, last - 1) - s + 1;         // no check among them but at s, never the last step
             if (use_tol) plain = std::min(plain, (s / K + 1) * K - s);
-            if (!check && plain >= 2) {
+            if (!check && fuse && plain >= 2) {
                 tile.steps = (int)std::min<int64_t>(plain, tile.halo);
                 launch_tangent_tile(c, a, tile);
                 cur ^= 1;

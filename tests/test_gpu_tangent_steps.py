@@ -1,0 +1,71 @@
+"""Fused tangent launches against one step per launch (needs a GPU): J, dJ,
+steps and residual are the same bits, checks between the launches included."""
+import numpy as np
+import pytest
+
+from paper_2609_31347_amd import inputs as I
+
+pytestmark = pytest.mark.gpu
+
+
+# intervals below, at and above the tiles' 7, 5 and 3 steps; one round of tiles with each, several rounds; ragged
+# tiles, a torus narrower than a region; a solve that converges and solves that end at max_steps
+@pytest.mark.parametrize("domain,nx,ny,K,tol,steps", [("plate", 48, 29, 1, 1e-300, 60), ("plate", 48, 29, 8, 1e-3, 200000),
+                                                     ("plate", 200, 120, 6, 1e-300, 61), ("plate", 301, 180, 4, 1e-300, 59),
+                                                     ("plate", 400, 240, 11, 1e-300, 60), ("periodic", 13, 9, 7, 1e-3, 4000),
+                                                     ("periodic", 65, 50, 9, 1e-300, 64), ("periodic", 300, 270, 5, 1e-300, 47)])
+@pytest.mark.parametrize("kind", ["force", "modes", "scalar", "E"])
+def test_tangent_tiles_equal_single_steps_bit_for_bit(domain, nx, ny, K, tol, steps, kind):
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_31347_amd import slbm as S
+    if domain == "plate":
+        cp = I.clamped_plate(nx, ny)
+        p = dict(nx=nx, ny=ny, dx=cp["dx"], domain=S.MASKED, node_mask=cp["active"].astype(np.uint8),
+                 link_bc=cp["bc"], link_wall=cp["wall"], link_normal=cp["normal"])
+    else:
+        p = dict(nx=nx, ny=ny, dx=1.0 / nx, domain=S.PERIODIC)
+    F = I.grf(nx, ny, p["dx"], 0.05, 0.1, 3, comps=2)
+    D = I.grf(nx, ny, p["dx"], 0.05, 0.2, 11, comps=2)
+    F -= F.mean((1, 2), keepdims=True)
+    p.update(E=1.0, nu=0.3, target=1e-6 * F[::-1].copy(), tol=tol, check_interval=K, max_steps=steps, fixed_force=F)
+    if kind == "force":
+        p.update(control_kind=S.CTRL_FORCE_NODAL)
+        c, d = F, D
+    elif kind == "modes":
+        p.update(control_kind=S.CTRL_FORCE_MODES, n_modes=2, force_modes=np.stack([F, D]))
+        c, d = np.array([0.7, -0.3]), np.array([0.2, 0.5])
+    elif kind == "scalar":
+        p.update(control_kind=S.CTRL_E_SCALAR_SQ)
+        c, d = np.array([1.05]), np.array([1.0])
+    else:
+        p.update(control_kind=S.CTRL_E_NODAL)
+        c, d = 1.0 + 0.3 * np.tanh(F[0] / F[0].std()), D[0]
+    out = []
+    for tuning in (1, -1):
+        ctx = S.solid_lbm_init(p)
+        S.solid_lbm_set_tuning(ctx, tuning, 0)
+        rc, J, dJ, info = S.tangent_solve(ctx, c, d)
+        out.append((rc, J, dJ, info.steps, info.residual))
+    assert out[0][2] != 0 and out[0][0] == (0 if tol > 1e-200 else 1)
+    assert out[0] == out[1]
+
+
+def test_one_step_per_launch_is_honoured():
+    """3000 steps of a 96 x 96 torus: launches of seven steps take less time than
+    single ones, and the setting chooses between them."""
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2609_31347_amd import slbm as S
+    F = I.grf(96, 96, 1 / 96, 0.05, 0.1, 3, comps=2)
+    p = dict(nx=96, ny=96, dx=1 / 96, domain=S.PERIODIC, E=1.0, nu=0.3, target=1e-6 * F, tol=0.0, max_steps=3000,
+             fixed_force=F, control_kind=S.CTRL_E_SCALAR_SQ)
+    ctx = S.solid_lbm_init(p)
+    ms = {}
+    for _ in range(2):
+        for tuning in (1, -1):
+            S.solid_lbm_set_tuning(ctx, tuning, 0)
+            ms[tuning] = S.tangent_solve(ctx, np.array([1.05]), np.array([1.0]))[3].device_ms
+    assert ms[1] > 1.4 * ms[-1]              # measured 2.4 times (40 x 40: 3.7 us per step against 1.5)
