@@ -693,7 +693,8 @@ int panel_tiles(const slbm_ctx* c, int R, int h)
 // taller ones (R = 3, 4, 6) were slower at every size, and a halo of 4 or 5
 // slower than 64 columns (371^2 1.85 against 1.64).  With a short check interval
 // the halo is the least that needs as many launches (K = 12: one of 12 steps,
-// whose first sweep is the check).
+// whose first sweep is the check); loops without checks take the widest (K = 1,
+// no tolerance, 32^2: 0.68 us per step, 1.47 with a halo of 4).
 // Then, in order of their time per step in one round (us per step, uniform
 // material, 100 - 250 workgroups): (R, h) = (3, 6) 1.6, (4, 8) 1.7, (4, 7) 1.85,
 // (6, 12) 1.88, (6, 10) 2.1, (8, 12) 2.4, (6, 8) 2.4; the first that fits is
@@ -704,7 +705,7 @@ int panel_tiles(const slbm_ctx* c, int R, int h)
 // with (3, 6) in several rounds (against LDS tiles: 700 x 651 6.4 -> 4.1,
 // 1024^2 13.3 -> 6.8).  (8, 12) spills with a modulus per node, so E fields do
 // not take it.
-bool panel_shape(const slbm_ctx* c, Fuse* f)
+bool panel_shape(const slbm_ctx* c, Fuse* f, bool checks)
 {
     if (c->masked || c->tb_T >= 0 || c->tile_w > 0) return false;
     if (c->tb_H > 0 && !use_tiles(c)) return false;          // rows set by the caller: wave strips
@@ -712,8 +713,10 @@ bool panel_shape(const slbm_ctx* c, Fuse* f)
     f->T = 1;
     for (int h = 14; h >= 6; --h) {
         if (panel_tiles(c, 2, h) > cus) continue;
-        const int64_t n = (c->K + h - 1) / h;            // launches between checks, and the least halo for as many
         f->R = 2;
+        f->TL = h;
+        if (!checks) return true;
+        const int64_t n = (c->K + h - 1) / h;            // launches between checks, and the least halo for as many
         f->TL = std::max(4, (int)((c->K + n - 1) / n));
         const int tiles = panel_tiles(c, 2, f->TL);
         if (tiles <= c->pcap) f->tiles = tiles;
@@ -1008,8 +1011,8 @@ void launch_strips(slbm_ctx* c, bool adjoint, const SweepArgs& s, const Fuse& f,
                        dim3(64 * kPipeS), pipe_lds_bytes<kPipeS>(), c->stream, a);
 }
 
-// Chooses the fused launches of a loop and builds what they need.
-int plan_fuse(slbm_ctx* c, Fuse* f)
+// Chooses the fused launches of a loop, with residual checks or without, and builds what they need.
+int plan_fuse(slbm_ctx* c, Fuse* f, bool checks)
 {
     if (c->masked && plate_shape(c, f)) {
         const int rc = build_panel_plan(c, f->R, f->TL);
@@ -1018,7 +1021,7 @@ int plan_fuse(slbm_ctx* c, Fuse* f)
         c->pshape[0] = 0;                // no memory for the plan (68 KiB per workgroup): LDS tiles
         *f = Fuse();
     }
-    if (panel_shape(c, f)) return SLBM_OK;
+    if (panel_shape(c, f, checks)) return SLBM_OK;
     if (pipe_shape(c, f)) return pipe_lds_limit(c);
     f->T = fused_steps(c);
     f->TL = tile_steps(c);
@@ -1293,7 +1296,7 @@ int run_loop(slbm_ctx* c, bool adjoint, int start, int64_t last, bool use_tol, i
     int cur = start;
     Fuse fuse;
     {
-        int rc = plan_fuse(c, &fuse);
+        int rc = plan_fuse(c, &fuse, use_tol);
         if (rc) return rc;
     }
     const int T = fuse.T, TL = fuse.TL;
@@ -2174,7 +2177,7 @@ int solid_lbm_time_sweeps(slbm_ctx* c, int32_t adjoint, int64_t n, double* ms)
     int cur = adjoint ? c->adj_cur : c->prim_cur;
     Fuse fuse;
     {
-        int rc = plan_fuse(c, &fuse);
+        int rc = plan_fuse(c, &fuse, false);
         if (rc) return rc;
     }
     const int TL = fuse.TL;
