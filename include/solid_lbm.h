@@ -283,7 +283,7 @@ int solid_lbm_time_sweeps(slbm_ctx *ctx, int32_t adjoint, int64_t n, double *ms)
  * uniform material, a pipeline of 8 waves with 16 steps beyond (fewer steps
  * before a check: wave strips; all wave strips of 8 steps if rows_per_wave is
  * set; thin grids LDS tiles or wave strips).  tangent_solve runs one step per
- * launch with 0 or 1, else tiles of its own (3, 5 or 7 steps).  rows_per_wave: rows each
+ * launch with 0 or 1, else tiles of its own (3, 5 or 7 steps) where they pay.  rows_per_wave: rows each
  * wave of a wave-strip launch covers (0 = automatic: as many as keep the wave
  * count at or below the device's SIMD count).  Every setting gives the same result bit for bit:
  * a fused launch performs exactly the arithmetic of its single sweeps.

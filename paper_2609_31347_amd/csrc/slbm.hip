@@ -1151,18 +1151,25 @@ void launch_tangent(slbm_ctx* c, const TangentArgs& a, bool check)
 }
 
 // Tile of the fused tangent launches: the most steps (7, 5, 3) whose tiles fit
-// the compute units at once, else 3.
-TangentTile tangent_tile(const slbm_ctx* c)
+// the compute units at once, else 3 steps in several rounds where the tiles'
+// nodes (halos left out) are at most 1.5 times the grid's, on plates up to 3
+// rounds; otherwise single steps (false).  us per step, single steps / tiles:
+// 400 x 240 plate (1.5 rounds) 10.0 / 7.0, 500 x 300 (2.4) 11.1 / 9.2, 700 x 420
+// (4.6) 13.2 / 13.3, 1300 x 780, E field, 43.5 / 48.3 (outside nodes cost a single
+// step nothing); torus 600^2 17.7 / 13.6, 5000 x 34 (1.4 times the nodes) 10.8 /
+// 9.5, 17 x 20000 (1.9) 16.0 / 20.3, 3 x 20000 (5.3) 4.65 / 9.76.
+bool tangent_tile(const slbm_ctx* c, TangentTile* t)
 {
-    TangentTile t;
     const int64_t cus = c->simds / 4;
+    int64_t tiles = 0;
     for (int h : {7, 5, 3}) {
-        t.halo = t.steps = h;
-        t.t = kTanSide - 2 * h;
-        t.tiles_x = (c->nx + t.t - 1) / t.t;
-        if ((int64_t)t.tiles_x * ((c->ny + t.t - 1) / t.t) <= cus) break;
+        t->halo = t->steps = h;
+        t->t = kTanSide - 2 * h;
+        t->tiles_x = (c->nx + t->t - 1) / t->t;
+        tiles = (int64_t)t->tiles_x * ((c->ny + t->t - 1) / t->t);
+        if (tiles <= cus) return true;
     }
-    return t;
+    return 2 * tiles * t->t * t->t <= 3 * c->N && (!c->masked || tiles <= 3 * cus);
 }
 
 void launch_tangent_tile(slbm_ctx* c, const TangentArgs& a, const TangentTile& t)
@@ -1186,8 +1193,8 @@ int tangent_loop(slbm_ctx* c, const TangentArgs& base, int64_t* t_out, int* x_ou
     const bool use_tol = c->tol > 0.0;
     const int64_t K = c->K, last = c->max_steps;
     TangentArgs a = base;
-    TangentTile tile = tangent_tile(c);
-    const bool fuse = c->tb_T < 0 || c->tb_T > 1;    // solid_lbm_set_tuning(ctx, 1, 0): one step per launch
+    TangentTile tile;
+    const bool fuse = tangent_tile(c, &tile) && (c->tb_T < 0 || c->tb_T > 1);   // steps per launch 0, 1: one at a time
     int cur = 0, last_in = 0;
     int64_t chunk = 0;
     int64_t s = 0;
