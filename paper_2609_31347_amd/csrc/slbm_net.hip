@@ -29,7 +29,8 @@ __device__ __forceinline__ float bf2f(uint16_t h) { return __uint_as_float((uint
 __host__ __device__ inline int kpad(int K) { return (K + 15) / 16 * 16; }
 
 // A workgroup's pixels: kTileY rows x kTileX columns of one image.
-constexpr int kTileX = 32, kTileY = 4;
+constexpr int kTileX = 32, kTileY = 4, kTilePix = kTileX * kTileY;
+constexpr int64_t kCus = 256;                // compute units of an MI355X
 constexpr size_t kStageMax = 136 * 1024;     // LDS bytes for the staged input region
 
 // Staged input region of a tile for dilation dil: the tile's pixels and their
@@ -68,28 +69,29 @@ __device__ __forceinline__ void stage_region(const uint16_t* __restrict__ xb, ui
 }
 
 // 3x3 convolution as an implicit GEMM on gfx950's v_mfma_f32_32x32x16_bf16:
-// one wave = 32 output channels x one row of kTileX pixels, four waves a tile
-// of 4 x 32.  The packed weights (A, rows = output channels) and, when it
-// fits (stage != 0), the tile's input region are first copied into LDS; the B
-// operand (the input at the 3x3 offsets, columns = pixels) is then gathered
-// from LDS: element k lies at the pixel's place plus an offset that a table in
-// LDS holds, and the region's zero rim stands for the padding, so a gathered
-// element is one add and one read.  128 consecutive pixels per workgroup,
-// whose whole rows had to fit, with a division and two bounds tests per element
-// took 50 us on average over the network's layers and data gradients (32
-// images of 64 x 39), this form 33; the copy of the region, up to 7 times the
-// tile at dilation 8, is most of what is left.  Operand lanes: row / column =
+// one wave = 32 output channels x 32 pixels, the packed weights (A, rows =
+// output channels) in LDS.  The B operand (the input at the 3x3 offsets, columns
+// = pixels) comes from one of two places.
+// STAGE: a workgroup's pixels are a tile of 4 x 32 (a wave a row of it) whose
+// input region is copied into LDS first; element k lies at the pixel's place plus
+// an offset that a table in LDS holds, and the region's zero rim stands for the
+// padding, so a gathered element is one add and one read.
+// Otherwise they are 128 consecutive pixels of the image, and every element is
+// read from memory (through the L1), with its division and bounds tests.
+// The copy of the region is what bounds the first, its instructions the second:
+// see fwd_staged.  Operand lanes: row / column =
 // lane % 32, k = 8 (lane / 32) + j, j < 8; result register r of lane l holds
 // row 8 (r / 4) + 4 (l / 32) + r % 4, column l % 32.
+template <bool STAGE>
 __global__ __launch_bounds__(256) void k_conv_fwd(const uint16_t* __restrict__ x, const uint16_t* __restrict__ w,
                                                  const float* __restrict__ bias, float* __restrict__ y,
                                                  uint16_t* __restrict__ yb, int Cin, int Cout, int H, int W,
-                                                 int Kp, int relu, int dil, int stage, int ntx, int wide)
+                                                 int Kp, int relu, int dil, int ntx, int wide)
 {
     extern __shared__ __align__(16) uint16_t smem[];
     const int wp = Kp + 8;                     // row of weights in LDS: 8 rows start on different banks
     uint16_t* wl = smem;                       // [32][wp] weights
-    int* off = reinterpret_cast<int*>(wl + 32 * wp);        // [Kp] offsets of k in the region (stage != 0)
+    int* off = reinterpret_cast<int*>(wl + 32 * wp);        // [Kp] offsets of k in the region (STAGE)
     uint16_t* xs = reinterpret_cast<uint16_t*>(off + Kp);   // the region
     const int HW = H * W, K = Cin * 9;
     const int tx = blockIdx.x % ntx, ty = blockIdx.x / ntx, b = blockIdx.y;
@@ -104,7 +106,7 @@ __global__ __launch_bounds__(256) void k_conv_fwd(const uint16_t* __restrict__ x
             for (int j = 0; j < 8; ++j) v[j] = (short)w[row * Kp + 8 * c + j];
         *reinterpret_cast<shortx8*>(wl + row * wp + 8 * c) = v;
     }
-    if (stage) {
+    if (STAGE) {
         for (int k = threadIdx.x; k < Kp; k += 256) {
             const int kk = k < K ? k : 0;                   // padding columns multiply zero weights by a staged value
             const int ci = kk / 9, tap = kk - ci * 9;
@@ -115,8 +117,10 @@ __global__ __launch_bounds__(256) void k_conv_fwd(const uint16_t* __restrict__ x
     __syncthreads();
     const int lane = threadIdx.x & 63, col = lane & 31, kq = (lane >> 5) * 8;
     const int wv = threadIdx.x >> 6;
-    const int py = ty * kTileY + wv, px = tx * kTileX + col;
-    const bool pv = py < H && px < W;
+    const int64_t q = (int64_t)blockIdx.x * kTilePix + 32 * wv + col;
+    const bool pv = STAGE ? ty * kTileY + wv < H && tx * kTileX + col < W : q < HW;
+    const int py = STAGE ? ty * kTileY + wv : pv ? (int)q / W : 0;
+    const int px = STAGE ? tx * kTileX + col : pv ? (int)q - py * W : 0;
     const uint16_t* xp = xs + (size_t)(wv * rw + col) * ph;
     floatx16 acc;
 #pragma unroll
@@ -124,7 +128,7 @@ __global__ __launch_bounds__(256) void k_conv_fwd(const uint16_t* __restrict__ x
     for (int kb = 0; kb < Kp; kb += 16) {
         const shortx8 av = *reinterpret_cast<const shortx8*>(wl + col * wp + kb + kq);
         shortx8 bv;
-        if (stage) {
+        if (STAGE) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) {
                 const short v = (short)xp[off[kb + kq + j]];
@@ -159,6 +163,24 @@ __global__ __launch_bounds__(256) void k_conv_fwd(const uint16_t* __restrict__ x
             if (yb) yb[o] = f2bf(v);
         }
     }
+}
+
+// Whether k_conv_fwd stages: a workgroup of 4 waves takes `lds` bytes of LDS, so
+// 160 KiB / lds of them run on a compute unit.  It does while all tiles run at
+// once, and beyond that while the copied regions hold at most 4 times the
+// image's pixels.  us, 32 -> 32 channels, from memory / staged (with a switch in one
+// kernel; by itself either form takes 1 - 2 us less): 32 images of 64 x
+// 39, dilation 1 36 / 18, 4 36 / 25, 8 (one workgroup of 84 KiB per compute unit,
+// 640 tiles) 36 / 82; one image of them, dilation 8, 26 / 20; 64 images of 128 x
+// 77, dilation 1 165 / 93, 4 164 / 152, 8 163 / 482; 32 images of 20 x 200 (2.5 and
+// 6 times the pixels), dilation 1 45 / 34, 4 45 / 59; 64 images of 10 x 256,
+// dilation 1 (5.1 times) 53 / 71.
+inline bool fwd_staged(int64_t B, int64_t H, int64_t W, int64_t dil, size_t lds)
+{
+    if (lds > 160 * 1024) return false;
+    const int64_t tiles = (W + kTileX - 1) / kTileX * ((H + kTileY - 1) / kTileY);
+    const int64_t at_once = kCus * std::min<int64_t>(8, 160 * 1024 / (int64_t)lds);
+    return B * tiles <= at_once || (kTileX + 2 * dil) * (kTileY + 2 * dil) * tiles <= 4 * H * W;
 }
 
 // Weight gradient as a GEMM on the FP32 MFMA v_mfma_f32_32x32x2_f32:
@@ -232,7 +254,6 @@ __global__ __launch_bounds__(1024) void k_conv_bwd_w(const float* __restrict__ d
 // workgroup per 32 columns (9 of 256 compute units), 48 us here plus 5 us for
 // the sum (the FP32 MFMAs alone take about 15 us).
 constexpr int kBwdRow = 33;                   // words of a staged dz pixel
-constexpr int kBwdPix = kTileX * kTileY;
 
 struct BwdSplit {
     int nb, parts, ntx, nty, run, nsplit;     // see above; run = tiles per workgroup
@@ -251,9 +272,9 @@ inline bool bwd_split(int64_t B, int Cin, int64_t H, int64_t W, int64_t dil, Bwd
     s->nty = (int)((H + kTileY - 1) / kTileY);
     const int64_t tiles = (int64_t)s->ntx * s->nty * B;
     if (tiles > INT32_MAX) return false;
-    s->run = (int)((tiles + 255) / 256);      // one workgroup per compute unit
+    s->run = (int)((tiles + kCus - 1) / kCus);   // one workgroup per compute unit
     s->nsplit = (int)((tiles + s->run - 1) / s->run);
-    s->lds = (size_t)kBwdPix * kBwdRow * sizeof(float) + xbytes;
+    s->lds = (size_t)kTilePix * kBwdRow * sizeof(float) + xbytes;
     s->words = (size_t)s->nsplit * s->parts * (s->nb * 32 + 1) * 32;
     return true;
 }
@@ -264,7 +285,7 @@ __global__ __launch_bounds__(1024) void k_conv_bwd_w_split(const float* __restri
 {
     extern __shared__ __align__(16) uint16_t smem[];
     float* zs = reinterpret_cast<float*>(smem);
-    uint16_t* xs = smem + kBwdPix * kBwdRow * 2;
+    uint16_t* xs = smem + kTilePix * kBwdRow * 2;
     const int HW = H * W, K = Cin * 9;
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63, row = lane & 31, half = lane >> 5;
     const int cb = wv % nb, part = wv / nb;
@@ -272,7 +293,7 @@ __global__ __launch_bounds__(1024) void k_conv_bwd_w_split(const float* __restri
     const int c = cb * 32 + row;                            // column (tap, ci) of this lane's B operand
     const int tap = c < K ? c / Cin : 0, ci = c < K ? c - tap * Cin : 0;
     const int xoff = ((tap / 3) * dil * rw + (tap % 3) * dil) * ph + ci;
-    const int per = kBwdPix / 2 / parts;                    // pixel pairs of this part
+    const int per = kTilePix / 2 / parts;                    // pixel pairs of this part
     floatx16 acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
@@ -282,8 +303,8 @@ __global__ __launch_bounds__(1024) void k_conv_bwd_w_split(const float* __restri
         const int b = t / (ntx * nty), tt = t - b * (ntx * nty), ty = tt / ntx, tx = tt - ty * ntx;
         __syncthreads();
         stage_region(x + (int64_t)b * Cin * HW, xs, Cin, H, W, dil, tx, ty);
-        for (int i = threadIdx.x; i < 32 * kBwdPix; i += blockDim.x) {
-            const int co = i / kBwdPix, p = i - co * kBwdPix;
+        for (int i = threadIdx.x; i < 32 * kTilePix; i += blockDim.x) {
+            const int co = i / kTilePix, p = i - co * kTilePix;
             const int yy = ty * kTileY + p / kTileX, xx = tx * kTileX + p % kTileX;
             const bool in = co < Cout && yy < H && xx < W;
             zs[p * kBwdRow + co] = in ? dz[((int64_t)b * Cout + co) * HW + yy * W + xx] : 0.0f;
@@ -479,22 +500,26 @@ int slbm_conv3x3_forward(const uint16_t* x, const uint16_t* w, const float* bias
 {
     if (!x || !w || !y || B < 1 || Cin < 1 || Cout < 1 || Cout > 32 || H < 1 || W < 1 || dilation < 1) return -1;
     const int Kp = kpad(Cin * 9);
-    const size_t wbytes = (size_t)32 * (Kp + 8) * sizeof(uint16_t) + (size_t)Kp * sizeof(int);
     const size_t xbytes = region_bytes(Cin, dilation);
+    size_t lds = (size_t)32 * (Kp + 8) * sizeof(uint16_t);
     if ((size_t)64 * Kp > 83 * 1024) return -3;   // over 147 input channels (LDS)
-    const int stage = xbytes <= kStageMax && wbytes + xbytes <= 160 * 1024 ? 1 : 0;
-    const size_t lds = wbytes + (stage ? xbytes : 0);
+    const int ntx = (W + kTileX - 1) / kTileX, nty = (H + kTileY - 1) / kTileY;
+    const size_t slds = lds + (size_t)Kp * sizeof(int) + (xbytes <= kStageMax ? xbytes : 0);
+    const bool stage = xbytes <= kStageMax && fwd_staged(B, H, W, dilation, slds);
+    if (stage) lds = slds;
     const int wide = ((uintptr_t)w & 15) == 0;   // 16-byte loads of the weights
     static bool attr = false;
     if (!attr) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_conv_fwd), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                160 * 1024) != hipSuccess)
+        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_conv_fwd<false>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess ||
+            hipFuncSetAttribute(reinterpret_cast<const void*>(&k_conv_fwd<true>),
+                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
             return -3;
         attr = true;
     }
-    const int ntx = (W + kTileX - 1) / kTileX, nty = (H + kTileY - 1) / kTileY;
-    hipLaunchKernelGGL(k_conv_fwd, dim3((unsigned)ntx * (unsigned)nty, (unsigned)B), dim3(256), lds,
-                       (hipStream_t)stream, x, w, bias, y, y_bf16, Cin, Cout, H, W, Kp, relu, dilation, stage, ntx, wide);
+    const dim3 grid(stage ? (unsigned)ntx * (unsigned)nty : blocks((int64_t)H * W, kTilePix), (unsigned)B);
+    hipLaunchKernelGGL(stage ? k_conv_fwd<true> : k_conv_fwd<false>, grid, dim3(256), lds, (hipStream_t)stream, x, w,
+                       bias, y, y_bf16, Cin, Cout, H, W, Kp, relu, dilation, ntx, wide);
     return status(hipGetLastError());
 }
 
