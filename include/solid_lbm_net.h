@@ -53,8 +53,8 @@ int slbm_conv3x3_backward_weight(const float *dz, const uint16_t *x, float *dw, 
  * not kept after the call; slbm_conv3x3_backward_weight_workspace gives the
  * bytes a layer takes, 0 if it has no such split: over 56 input channels, or
  * a dilation whose input region exceeds the LDS), and a second kernel adds
- * them in a fixed order.  With ws NULL or too small it is
- * slbm_conv3x3_backward_weight. */
+ * them in a fixed order.  With ws NULL or too small, or at most 384 pixels in
+ * all (576 with over 16 input channels), it is slbm_conv3x3_backward_weight. */
 int64_t slbm_conv3x3_backward_weight_workspace(int32_t B, int32_t Cin, int32_t H, int32_t W, int32_t dilation);
 int slbm_conv3x3_backward_weight_ws(const float *dz, const uint16_t *x, float *dw, float *db, int32_t B,
                                     int32_t Cin, int32_t Cout, int32_t H, int32_t W, int32_t dilation, void *ws,

@@ -254,6 +254,10 @@ __global__ __launch_bounds__(1024) void k_conv_bwd_w(const float* __restrict__ d
 // workgroup per 32 columns (9 of 256 compute units), 48 us here plus 5 us for
 // the sum (the FP32 MFMAs alone take about 15 us).
 constexpr int kBwdRow = 33;                   // words of a staged dz pixel
+// Pixels that the unsplit kernel still does in less time (us, unsplit / split: 32
+// channels, 100 pixels 8.4 / 14.1, 256 8.9 / 15.0, 520 14.8 / 18.9, 676 18.7 /
+// 15.2; 7 channels, 256 8.8 / 11.3, 400 11.8 / 11.1).
+inline int64_t bwd_few(int Cin) { return Cin > 16 ? 576 : 384; }
 
 struct BwdSplit {
     int nb, parts, ntx, nty, run, nsplit;     // see above; run = tiles per workgroup
@@ -536,7 +540,8 @@ int slbm_conv3x3_backward_weight_ws(const float* dz, const uint16_t* x, float* d
 {
     if (!dz || !x || !dw || B < 1 || Cin < 1 || Cout < 1 || Cout > 32 || H < 1 || W < 1 || dilation < 1) return -1;
     BwdSplit s;
-    if (!ws || !bwd_split(B, Cin, H, W, dilation, &s) || ws_bytes < (int64_t)(s.words * sizeof(float)))
+    if (!ws || (int64_t)B * H * W <= bwd_few(Cin) || !bwd_split(B, Cin, H, W, dilation, &s) ||
+        ws_bytes < (int64_t)(s.words * sizeof(float)))
         return slbm_conv3x3_backward_weight(dz, x, dw, db, B, Cin, Cout, H, W, dilation, stream);
     static bool attr = false;
     if (!attr) {
