@@ -703,7 +703,10 @@ int panel_tiles(const slbm_ctx* c, int R, int h)
 // panels of (8, 8), which fit to 768^2; 800^2: 3.6 against 4.25 with (8, 7);
 // 600^2: 2.98 against 2.62 with (8, 12)).  E fields have no pipeline and go on
 // with (3, 6) in several rounds (against LDS tiles: 700 x 651 6.4 -> 4.1,
-// 1024^2 13.3 -> 6.8).  (8, 12) spills with a modulus per node, so E fields do
+// 1024^2 13.3 -> 6.8), unless that takes over 1.5 times the workgroups per step:
+// an LDS tile's workgroup costs about 0.6 of a panel's, and grids of up to 20
+// columns leave most of a panel's 64 unused (3 x 40000 9.37 us per step in LDS
+// tiles, 9.98 in panels; 17 x 20000 5.2 / 6.1; 40 x 16384 8.6 / 5.5).  (8, 12) spills with a modulus per node, so E fields do
 // not take it.
 bool panel_shape(const slbm_ctx* c, Fuse* f, bool checks)
 {
@@ -732,6 +735,11 @@ bool panel_shape(const slbm_ctx* c, Fuse* f, bool checks)
         return true;
     }
     if (!c->efield_on) return false;
+    int tw, th;
+    const int lh = tile_halo(c, false);
+    tile_shape(c, lh, &tw, &th);
+    const int64_t lds = (int64_t)((c->nx + tw - 1) / tw) * ((c->ny + th - 1) / th);
+    if (2 * lh * (int64_t)panel_tiles(c, 3, 6) > 3 * 6 * lds) return false;
     f->R = 3;
     f->TL = 6;
     f->T = 1;
