@@ -865,7 +865,13 @@ double plate_launch_us(int rims, int inners, int m, double tr, double ti)
 // every size measured (us per primal step): 340 x 204 to 420 x 252 (2, 8) 2.3
 // against 2.6 - 2.7 with (3, 8), 450 x 270 (3, 8) 2.69, 512 x 308 (3, 8) 2.65 -
 // 3.73, 700 x 420 (4, 8) 3.42 - 4.57, 850 x 510 (4, 6) 4.29 - 5.69, 1000 x 600
-// (4, 6) 5.81 - 7.64.  A region must not hold more boundary nodes than the
+// (4, 6) 5.81 - 7.64.  Where the LDS tiles too need several rounds of workgroups
+// they take 1.5 to 2.1 us per step and round; a panel shape of more than 1.87 is
+// not taken: narrow columns of a width that suits no shape, with boundary nodes
+// in every tile (mean of primal and adjoint, LDS tiles / panels: 60 x 8000 8.9 /
+// 10.2, 60 x 5000 5.9 / 6.8, 100 x 8000 13.6 / 14.4; 64 x 8000 12.8 / 10.1, 40 x
+// 4000 3.9 / 3.2, 8000 x 60 8.7 / 6.3 and all plates of the usual 5 : 3 take
+// panels).  A region must not hold more boundary nodes than the
 // boundary waves have lanes; plates with denser rims keep the LDS tiles.
 bool plate_shape(slbm_ctx* c, Fuse* f)
 {
@@ -891,6 +897,10 @@ bool plate_shape(slbm_ctx* c, Fuse* f)
                 c->pshape[1] = h;
                 c->plive = std::move(t.list);
             }
+            int tw, th;
+            tile_shape(c, tile_halo(c, false), &tw, &th);
+            const int64_t rounds = ((int64_t)((c->nx + tw - 1) / tw) * ((c->ny + th - 1) / th) + cus - 1) / cus;
+            if (rounds > 1 && best > 1.87 * rounds) c->pshape[0] = 0;
         }
     }
     if (c->pshape[0] == 0) return false;
