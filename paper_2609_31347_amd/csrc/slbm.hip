@@ -2999,6 +2999,17 @@ int batch_loop(slbm_batch* b, bool adjoint, std::vector<int64_t>& t_out, std::ve
     if (cls.size() == 1) cls[0].stream = b->stream;
     auto last_report = std::chrono::steady_clock::now();
     int64_t reported = -1;
+    // an error leaves the loop with launches of both classes queued: what runs next on b->stream is not
+    // ordered after those on b->pstream
+    struct Drain {
+        slbm_batch* b;
+        ~Drain()
+        {
+            if (!b) return;
+            (void)hipStreamSynchronize(b->pstream);
+            (void)hipStreamSynchronize(b->stream);
+        }
+    } drain{cls.size() == 2 ? b : nullptr};
     BHIPCHK(b, hipEventRecord(b->t0, b->stream));
     if (cls.size() == 2) BHIPCHK(b, hipStreamWaitEvent(b->pstream, b->t0, 0));
     for (;;) {
@@ -3044,6 +3055,7 @@ int batch_loop(slbm_batch* b, bool adjoint, std::vector<int64_t>& t_out, std::ve
     }
     BHIPCHK(b, hipEventRecord(b->t1, b->stream));
     BHIPCHK(b, hipStreamSynchronize(b->stream));
+    drain.b = nullptr;
     float f = 0.f;
     BHIPCHK(b, hipEventElapsedTime(&f, b->t0, b->t1));
     if (dev_ms) *dev_ms = f;

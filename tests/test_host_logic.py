@@ -1,0 +1,86 @@
+"""The library's host side on a stubbed HIP runtime (hip_stub.c; no GPU): waits
+after a failed launch."""
+import os
+import subprocess
+import sys
+import textwrap
+
+import pytest
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+ROOT = os.path.dirname(HERE)
+
+PRELUDE = """
+import ctypes, os, sys
+sys.modules["torch"] = None                    # its own HIP runtime would answer first
+stub = ctypes.CDLL({stub!r}, mode=ctypes.RTLD_GLOBAL)
+for f in ("stub_what", "stub_where"):
+    getattr(stub, f).restype = ctypes.c_size_t
+sys.path.insert(0, {root!r})
+import numpy as np
+from paper_2609_31347_amd import inputs as I, slbm as S
+LAUNCH, SYNC, ATTR = 1, 2, 3
+def log():
+    return [(stub.stub_op(i), stub.stub_what(i), stub.stub_where(i)) for i in range(stub.stub_size())]
+"""
+
+
+@pytest.fixture(scope="module")
+def stub(tmp_path_factory):
+    """The stub, under the runtime's name, so that the library binds to it."""
+    d = tmp_path_factory.mktemp("hip_stub")
+    out, vers = os.path.join(d, "libamdhip64.so.7"), os.path.join(d, "versions")
+    with open(vers, "w", encoding="utf-8") as f:
+        f.write("hip_4.2 { *; };\nhip_4.3 { hipGraph*; hipStreamBeginCapture; hipStreamEndCapture; };\n")
+    subprocess.run(["gcc", "-O1", "-fPIC", "-shared", "-Wall", "-Wl,-soname,libamdhip64.so.7",
+                    "-Wl,--version-script," + vers, "-o", out, os.path.join(HERE, "hip_stub.c")], check=True)
+    return out
+
+
+def run(stub, code):
+    src = PRELUDE.format(stub=stub, root=ROOT) + textwrap.dedent(code)
+    r = subprocess.run([sys.executable, "-c", src], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout + r.stderr
+    return r.stdout
+
+
+def test_a_batch_waits_for_both_streams_when_a_launch_fails(stub):
+    """Kernels of the other class may still run on their stream: the call that
+    reports the error returns only after they have ended, like every other call."""
+    out = run(stub, """
+        n = 32
+        cp = I.clamped_plate(32, 20)
+        probs = [dict(nx=n, ny=n, dx=1 / n, E=1.0, nu=0.3, target=np.ones((2, n, n)), control_kind=S.CTRL_FORCE_NODAL),
+                 dict(nx=32, ny=20, dx=cp["dx"], E=1.0, nu=0.3, domain=S.MASKED,
+                      node_mask=cp["active"].astype(np.uint8), link_bc=cp["bc"], link_wall=cp["wall"],
+                      link_normal=cp["normal"], target=np.ones((2, 20, 32)), control_kind=S.CTRL_FORCE_NODAL)]
+        for p in probs:
+            p.update(tol=1e-10, max_steps=200, check_interval=10)
+        controls = [np.ones((2, n, n)), np.ones((2, 20, 32))]
+        b = S.solid_lbm_batch_init(probs)
+        S.batch_objective_and_grad(b, controls, want_grad=False)      # builds the launch plans
+        stub.stub_reset(-1)
+        S.batch_objective_and_grad(b, controls, want_grad=False)
+        whole = log()
+        streams = {w for op, _, w in whole if op == LAUNCH}
+        assert len(streams) == 2                                     # one per class
+        other = [w for w in streams if w][0]
+        mine = [i for i, e in enumerate(e for e in whole if e[0] == LAUNCH) if e[2] == other]
+        for at in (mine[0], mine[len(mine) // 2], mine[-1], mine[len(mine) // 2] + 1):
+            stub.stub_reset(at)
+            try:
+                S.batch_objective_and_grad(b, controls, want_grad=False)
+            except S.SlbmError as e:
+                assert e.code == S.EHIP
+            else:
+                raise AssertionError("no error")
+            part = log()
+            for s in streams:
+                last = max([i for i, e in enumerate(part) if e[0] == LAUNCH and e[2] == s], default=-1)
+                assert any(e[0] == SYNC and e[2] in (s, 2 ** 64 - 1) for e in part[last + 1:]), (at, s)
+        stub.stub_reset(-1)
+        S.batch_objective_and_grad(b, controls, want_grad=False)      # the batch is usable afterwards
+        assert len(log()) == len(whole)
+        print("ok")
+    """)
+    assert out.strip() == "ok"
