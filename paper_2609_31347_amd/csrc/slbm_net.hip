@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <atomic>
 #include <type_traits>
 
 #include "solid_lbm_net.h"
@@ -494,6 +495,19 @@ inline unsigned blocks(int64_t n, int b) { return (unsigned)((n + b - 1) / b); }
 
 int status(hipError_t e) { return e == hipSuccess ? 0 : -3; }
 
+// Lets a kernel use the whole LDS of the current device; `done` holds a bit per
+// device on which that has been set (the attribute belongs to the device).
+int allow_lds(const void* kernel, std::atomic<uint64_t>& done)
+{
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return -3;
+    const uint64_t bit = dev < 64 ? 1ull << dev : 0;
+    if (done.load(std::memory_order_relaxed) & bit) return 0;
+    if (hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess) return -3;
+    done.fetch_or(bit, std::memory_order_relaxed);
+    return 0;
+}
+
 }  // namespace
 
 extern "C" {
@@ -512,15 +526,10 @@ int slbm_conv3x3_forward(const uint16_t* x, const uint16_t* w, const float* bias
     const bool stage = xbytes <= kStageMax && fwd_staged(B, H, W, dilation, slds);
     if (stage) lds = slds;
     const int wide = ((uintptr_t)w & 15) == 0;   // 16-byte loads of the weights
-    static bool attr = false;
-    if (!attr) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_conv_fwd<false>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess ||
-            hipFuncSetAttribute(reinterpret_cast<const void*>(&k_conv_fwd<true>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
-            return -3;
-        attr = true;
-    }
+    static std::atomic<uint64_t> fwd_mem{0}, fwd_staged_form{0};
+    const int rc = stage ? allow_lds(reinterpret_cast<const void*>(&k_conv_fwd<true>), fwd_staged_form)
+                         : allow_lds(reinterpret_cast<const void*>(&k_conv_fwd<false>), fwd_mem);
+    if (rc) return rc;
     const dim3 grid(stage ? (unsigned)ntx * (unsigned)nty : blocks((int64_t)H * W, kTilePix), (unsigned)B);
     hipLaunchKernelGGL(stage ? k_conv_fwd<true> : k_conv_fwd<false>, grid, dim3(256), lds, (hipStream_t)stream, x, w,
                        bias, y, y_bf16, Cin, Cout, H, W, Kp, relu, dilation, ntx, wide);
@@ -543,13 +552,9 @@ int slbm_conv3x3_backward_weight_ws(const float* dz, const uint16_t* x, float* d
     if (!ws || (int64_t)B * H * W <= bwd_few(Cin) || !bwd_split(B, Cin, H, W, dilation, &s) ||
         ws_bytes < (int64_t)(s.words * sizeof(float)))
         return slbm_conv3x3_backward_weight(dz, x, dw, db, B, Cin, Cout, H, W, dilation, stream);
-    static bool attr = false;
-    if (!attr) {
-        if (hipFuncSetAttribute(reinterpret_cast<const void*>(&k_conv_bwd_w_split),
-                                hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024) != hipSuccess)
-            return -3;
-        attr = true;
-    }
+    static std::atomic<uint64_t> split{0};
+    const int rc = allow_lds(reinterpret_cast<const void*>(&k_conv_bwd_w_split), split);
+    if (rc) return rc;
     hipLaunchKernelGGL(k_conv_bwd_w_split, dim3((unsigned)s.nsplit), dim3(64u * s.nb * s.parts), s.lds,
                        (hipStream_t)stream, dz, x, (float*)ws, B, Cin, Cout, H, W, dilation, s.nb, s.parts, s.ntx,
                        s.nty, s.run);

@@ -1,5 +1,5 @@
 """The library's host side on a stubbed HIP runtime (hip_stub.c; no GPU): waits
-after a failed launch."""
+after a failed launch, kernel attributes of every device."""
 import os
 import subprocess
 import sys
@@ -81,6 +81,36 @@ def test_a_batch_waits_for_both_streams_when_a_launch_fails(stub):
         stub.stub_reset(-1)
         S.batch_objective_and_grad(b, controls, want_grad=False)      # the batch is usable afterwards
         assert len(log()) == len(whole)
+        print("ok")
+    """)
+    assert out.strip() == "ok"
+
+
+@pytest.mark.parametrize("what", ["forward, staged", "forward, from memory", "weight gradient"])
+def test_convolutions_raise_the_lds_limit_on_every_device(stub, what):
+    """The limit of dynamic LDS is set on each device before the first launch
+    there, and once."""
+    out = run(stub, f"""
+        what = {what!r}
+        """ + """
+        L, P = S.LIB, ctypes.c_void_p
+        buf = (ctypes.c_char * 64)()
+        p = P(ctypes.addressof(buf))
+        def call():
+            if what == "weight gradient":
+                L.slbm_conv3x3_backward_weight_workspace.restype = ctypes.c_int64
+                n = L.slbm_conv3x3_backward_weight_workspace(8, 32, 39, 64, 1)
+                return L.slbm_conv3x3_backward_weight_ws(p, p, p, p, 8, 32, 32, 39, 64, 1, p, ctypes.c_int64(n), None)
+            return L.slbm_conv3x3_forward(p, p, p, p, None, 8, 32, 32, 39, 64, 0, 1 if "staged" in what else 40, None)
+        for dev, sets in ((0, 1), (1, 1), (0, 0), (5, 1), (1, 0), (70, 1), (70, 1)):
+            stub.stub_device(dev)
+            stub.stub_reset(-1)
+            assert call() == 0
+            seen = log()
+            attrs = [e for e in seen if e[0] == ATTR]
+            assert len(attrs) == sets and all(e[2] == dev for e in attrs), (dev, attrs)
+            assert [e[0] for e in seen][:sets + 1] == [ATTR] * sets + [LAUNCH]
+            assert all(e[1] == seen[sets][1] for e in attrs)          # of the kernel that is launched
         print("ok")
     """)
     assert out.strip() == "ok"
