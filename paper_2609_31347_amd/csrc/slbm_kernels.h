@@ -1430,17 +1430,6 @@ __device__ __forceinline__ void tile_body(const TileArgs& a, int tile, double* l
             if (w < nwords) lw[w] = rw[p];
         }
     }
-    double s0[CHECK ? kTileNPT : 1], s1[CHECK ? kTileNPT : 1];
-    bool own[CHECK ? kTileNPT : 1];                  // nodes of the tile proper
-    if (CHECK) {
-#pragma unroll
-        for (int j = 0; j < kTileNPT; ++j) {
-            own[j] = ni[j] < R && cd[j] >= 0 && rx[j] >= h && rx[j] < RX - h && ry[j] >= h && ry[j] < RY - h &&
-                     x0 + rx[j] < nx && y0 + ry[j] < ny;
-            s0[j] = own[j] ? ldg(a.snap + gn[j]) : 0.0;
-            s1[j] = own[j] ? ldg(a.snap + N + gn[j]) : 0.0;
-        }
-    }
     __syncthreads();
     for (int s = 1; s <= a.steps; ++s) {
         const bool last = s == a.steps;
@@ -1465,10 +1454,29 @@ __device__ __forceinline__ void tile_body(const TileArgs& a, int tile, double* l
                 const int off = cx(q) + cy(q) * RX;
                 f[q] = cur[q * R + (ADJ ? i + off : i - off)];
             }
+            // a check's sums; the last snapshot is read here (held from the start of the launch it took the plates'
+            // registers over the 128 of four waves per SIMD)
+            const bool sums = CHECK && s == 1 && rx[j] >= h && rx[j] < RX - h && ry[j] >= h && ry[j] < RY - h &&
+                              x0 + rx[j] < nx && y0 + ry[j] < ny;
+            auto tally = [&](double d0, double d1) {
+                const double s0 = ldg(a.snap + n), s1 = ldg(a.snap + N + n);
+                num += (d0 - s0) * (d0 - s0) + (d1 - s1) * (d1 - s1);
+                den += d0 * d0 + d1 * d1;
+                stg(a.snap + n, d0);
+                stg(a.snap + N + n, d1);
+            };
             double d0 = 0.0, d1 = 0.0;
             if (CHECK && ADJ) {
                 d0 = (f[0] - f[2]) + (f[4] - f[5]) + (f[7] - f[6]);
                 d1 = (f[1] - f[3]) + (f[4] + f[5]) - (f[6] + f[7]);
+            }
+            if (!ADJ && sums) {                      // before the collision, for the same reason
+                if (!MASKED || code == 0)            // as collide_bulk
+                    tally(fma(0.5, c0[j], (f[0] - f[2]) + ((f[4] - f[5]) - (f[6] - f[7]))),
+                          fma(0.5, c1[j], (f[1] - f[3]) + ((f[4] + f[5]) - (f[6] + f[7]))));
+                else                                 // as node_map
+                    tally(fma(0.5, c0[j], f[0] - f[2] + f[4] - f[5] - f[6] + f[7]),
+                          fma(0.5, c1[j], f[1] - f[3] + f[4] + f[5] - f[6] - f[7]));
             }
             if (!ADJ) {
                 if (!MASKED || code == 0) {
@@ -1479,8 +1487,6 @@ __device__ __forceinline__ void tile_body(const TileArgs& a, int tile, double* l
                     auto bnode = [&](const BNode* bn) {
                         double gg[2] = {c0[j], c1[j]}, fC[8], hv[8], mb[5];
                         node_map<double>(f, gg, rl[j], bn, true, fC, hv, mb);
-                        d0 = mb[0];
-                        d1 = mb[1];
                         const uint32_t cut = bn->cut;
                         int64_t idx[8];
                         // the last sweep covers nodes of the grid proper only (no wrap)
@@ -1515,12 +1521,7 @@ __device__ __forceinline__ void tile_body(const TileArgs& a, int tile, double* l
                     else bnode(bng[j]);
                 }
             }
-            if (CHECK && s == 1 && own[j]) {
-                num += (d0 - s0[j]) * (d0 - s0[j]) + (d1 - s1[j]) * (d1 - s1[j]);
-                den += d0 * d0 + d1 * d1;
-                stg(a.snap + n, d0);
-                stg(a.snap + N + n, d1);
-            }
+            if (ADJ && sums) tally(d0, d1);
             if (last) {
 #pragma unroll
                 for (int q = 0; q < 8; ++q) stg(a.dst + q * N + n, out[j][q]);
