@@ -186,8 +186,8 @@ struct slbm_ctx {
     int2* pplan = nullptr;
     double* pplan_coef = nullptr;
     int32_t* pplan_n = nullptr;
-    int32_t* ptiles = nullptr;
-    std::vector<int32_t> plive;  // tiles with domain nodes, by workgroup
+    int2* ptiles = nullptr;
+    std::vector<int2> plive;     // by workgroup: a tile with domain nodes, its place in the plan (-1: no boundary nodes)
     std::vector<uint8_t> mask;   // plates: node_mask
     int pshape[2] = {-1, 0};     // rows per lane (-1: not looked for yet, 0: no panels), halo
     int64_t nblk = 0;  // blocks of one sweep
@@ -786,7 +786,7 @@ void launch_panel(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, cons
 // Tiles of a plate's panel shape that write at least one domain node, in the
 // order of the workgroups that run them.
 struct PlateTiles {
-    std::vector<int32_t> list;
+    std::vector<int2> list;      // tile, number among the rim tiles (-1: an inner tile)
     int rim = 0;      // tiles with boundary nodes in their region
     int most = 0;     // most boundary nodes of a region (halo and periodic copies included)
 };
@@ -811,6 +811,7 @@ PlateTiles plate_tiles(const slbm_ctx* c, int R, int h)
         for (int j : by)
             for (int i : bx) out.most = std::max(out.most, ++count[(size_t)j * tx + i]);
     }
+    std::vector<int32_t> rim, inner;
     for (int j = 0; j < ty; ++j)
         for (int i = 0; i < tx; ++i) {
             bool live = false;
@@ -818,15 +819,14 @@ PlateTiles plate_tiles(const slbm_ctx* c, int R, int h)
                 const uint8_t* m = c->mask.data() + (int64_t)y * c->nx;
                 live = std::any_of(m + i * tw, m + std::min((i + 1) * tw, c->nx), [](uint8_t v) { return v != 0; });
             }
-            if (live) out.list.push_back(j * tx + i);
+            if (live) (count[(size_t)j * tx + i] ? rim : inner).push_back(j * tx + i);
         }
     // Workgroup b runs entry xcd_order(b) of the list, which hands XCD x one run
     // of it.  Each run gets its share of the slow rim tiles first, then of the
     // inner tiles, both contiguous in the grid: no XCD has more rim tiles than
     // the others, and its last round is made of inner tiles.
-    std::vector<int32_t> rim, inner;
-    for (int32_t t : out.list) (count[t] ? rim : inner).push_back(t);
-    const size_t n = out.list.size(), nr = rim.size();
+    const size_t n = rim.size() + inner.size(), nr = rim.size();
+    out.list.resize(n);
     out.rim = (int)nr;
     size_t ri = 0, ii = 0, at = 0;
     for (size_t x = 0; x < kXcds; ++x) {
@@ -834,7 +834,10 @@ PlateTiles plate_tiles(const slbm_ctx* c, int R, int h)
         size_t r = nr / kXcds + (x < nr % kXcds ? 1 : 0);
         r = std::min(r, len);
         if (x == kXcds - 1) r = nr - ri;                 // what is left fits: at + len = n
-        for (size_t k = 0; k < len; ++k) out.list[at++] = k < r ? rim[ri++] : inner[ii++];
+        for (size_t k = 0; k < len; ++k, ++at) {
+            out.list[at] = k < r ? make_int2(rim[ri], (int)ri) : make_int2(inner[ii], -1);
+            ++(k < r ? ri : ii);
+        }
     }
     return out;
 }
@@ -910,11 +913,12 @@ bool plate_shape(slbm_ctx* c, Fuse* f)
     return true;
 }
 
-// Builds the launch plan of a plate's panels for c->plive, once.
+// Builds the launch plan of a plate's panels for c->plive, once: 66 KiB per tile with boundary nodes.
 int build_panel_plan(slbm_ctx* c, int R, int h)
 {
     if (c->pplan_n) return SLBM_OK;
     const int64_t wgs = (int64_t)c->plive.size();
+    const int64_t rims = std::count_if(c->plive.begin(), c->plive.end(), [](const int2& t) { return t.y >= 0; });
     int rc;
     const void* fns[4] = {reinterpret_cast<const void*>(panel_kernel(true, false, false, R)),
                           reinterpret_cast<const void*>(panel_kernel(true, false, true, R)),
@@ -922,8 +926,8 @@ int build_panel_plan(slbm_ctx* c, int R, int h)
                           reinterpret_cast<const void*>(panel_kernel(true, true, true, R))};
     for (const void* fn : fns)
         HIPCHK(c, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPlateLds));
-    const size_t bytes[4] = {(size_t)wgs * kPanelCap * sizeof(int2), (size_t)wgs * kPanelCap * 32 * sizeof(double),
-                             (size_t)wgs * sizeof(int32_t), (size_t)wgs * sizeof(int32_t)};
+    const size_t bytes[4] = {(size_t)rims * kPanelCap * sizeof(int2), (size_t)rims * kPanelCap * 32 * sizeof(double),
+                             (size_t)wgs * sizeof(int2), (size_t)wgs * sizeof(int32_t)};
     void* p[4] = {};
     for (int k = 0; k < 4; ++k)
         if ((rc = dalloc(c, &p[k], bytes[k]))) {
@@ -932,9 +936,9 @@ int build_panel_plan(slbm_ctx* c, int R, int h)
         }
     int2* plan = (int2*)p[0];
     double* coef = (double*)p[1];
-    c->ptiles = (int32_t*)p[2];
+    c->ptiles = (int2*)p[2];
     int32_t* count = (int32_t*)p[3];
-    HIPCHK(c, hipMemcpyAsync(c->ptiles, c->plive.data(), (size_t)wgs * sizeof(int32_t), hipMemcpyHostToDevice,
+    HIPCHK(c, hipMemcpyAsync(c->ptiles, c->plive.data(), (size_t)wgs * sizeof(int2), hipMemcpyHostToDevice,
                              c->stream));
     PanelArgs a;
     std::memset(&a, 0, sizeof(a));
@@ -1036,7 +1040,7 @@ int plan_fuse(slbm_ctx* c, Fuse* f, bool checks)
         const int rc = build_panel_plan(c, f->R, f->TL);
         if (rc != SLBM_ENOMEM) return rc;
         (void)hipGetLastError();
-        c->pshape[0] = 0;                // no memory for the plan (68 KiB per workgroup): LDS tiles
+        c->pshape[0] = 0;                // no memory for the plan: LDS tiles
         *f = Fuse();
     }
     if (panel_shape(c, f, checks)) return SLBM_OK;

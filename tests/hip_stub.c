@@ -1,13 +1,13 @@
 /* A HIP runtime for tests of the library's host side without a GPU: device
  * memory is host memory, copies are memcpy, kernels do not run.  Launches,
- * waits and attribute settings are logged in order with their stream (or
- * device), and one launch can be made to fail. */
+ * waits, attribute settings and allocations are logged in order with their
+ * stream (device, bytes), and one launch can be made to fail. */
 #include <stdlib.h>
 #include <string.h>
 
 typedef struct { unsigned x, y, z; } dim3;
 typedef void *stream_t;
-enum { LAUNCH = 1, SYNC = 2, ATTR = 3 };
+enum { LAUNCH = 1, SYNC = 2, ATTR = 3, ALLOC = 4 };
 enum { SUCCESS = 0, FAILED = 719 };
 
 static struct { int op; const void *what, *where; } entries[1 << 20];
@@ -78,7 +78,7 @@ int hipFuncSetAttribute(const void *f, int what, int v) { (void)what, (void)v; p
 int hipFuncGetAttributes(void *a, const void *f) { (void)a, (void)f; return FAILED; }
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *f, int b, size_t l) { (void)f, (void)b, (void)l; *n = 1; return SUCCESS; }
 int hipGetSymbolAddress(void **p, const void *s) { (void)s; *p = 0; return FAILED; }
-int hipMalloc(void **p, size_t n) { *p = calloc(n, 1); return *p ? SUCCESS : 2; }
+int hipMalloc(void **p, size_t n) { put(ALLOC, (void *)n, 0); *p = calloc(n, 1); return *p ? SUCCESS : 2; }
 int hipFree(void *p) { free(p); return SUCCESS; }
 int hipHostMalloc(void **p, size_t n, unsigned f) { (void)f; return hipMalloc(p, n); }
 int hipHostFree(void *p) { free(p); return SUCCESS; }

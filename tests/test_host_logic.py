@@ -1,5 +1,5 @@
 """The library's host side on a stubbed HIP runtime (hip_stub.c; no GPU): waits
-after a failed launch, kernel attributes of every device."""
+after a failed launch, kernel attributes of every device, memory of launch plans."""
 import os
 import subprocess
 import sys
@@ -19,7 +19,7 @@ for f in ("stub_what", "stub_where"):
 sys.path.insert(0, {root!r})
 import numpy as np
 from paper_2609_31347_amd import inputs as I, slbm as S
-LAUNCH, SYNC, ATTR = 1, 2, 3
+LAUNCH, SYNC, ATTR, ALLOC = 1, 2, 3, 4
 def log():
     return [(stub.stub_op(i), stub.stub_what(i), stub.stub_where(i)) for i in range(stub.stub_size())]
 """
@@ -114,3 +114,25 @@ def test_convolutions_raise_the_lds_limit_on_every_device(stub, what):
         print("ok")
     """)
     assert out.strip() == "ok"
+
+
+def test_panel_plans_take_memory_for_rim_tiles_only(stub):
+    """The first solve of a 1000 x 600 plate allocates less for its panels than the
+    16 KiB per 20 x 20 tile of the LDS tiles' plan."""
+    out = run(stub, """
+        cp = I.clamped_plate(1000, 600)
+        p = dict(nx=1000, ny=600, dx=cp["dx"], E=1.0, nu=0.3, domain=S.MASKED, node_mask=cp["active"].astype(np.uint8),
+                 link_bc=cp["bc"], link_wall=cp["wall"], link_normal=cp["normal"], target=np.ones((2, 600, 1000)),
+                 control_kind=S.CTRL_FORCE_NODAL, tol=0.0, max_steps=13)
+        taken = {}
+        for tuning in (-1, 6):
+            ctx = S.solid_lbm_init(p)
+            S.solid_lbm_set_tuning(ctx, tuning, 0)
+            stub.stub_reset(-1)
+            S.objective_and_grad(ctx, np.ones((2, 600, 1000)), want_grad=False)
+            taken[tuning] = sum(n for op, n, _ in log() if op == ALLOC)
+        print(taken[-1], taken[6], flush=True)
+        assert 0 < taken[-1] < taken[6]
+    """)
+    panels, tiles = (int(v) for v in out.split())
+    assert panels < 0.6 * tiles
