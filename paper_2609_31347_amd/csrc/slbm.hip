@@ -175,6 +175,7 @@ struct slbm_ctx {
     void* progress_user = nullptr;
     double progress_every = 0.0;          // seconds between reports
     bool tile_attr = false;      // LDS limits of the plate tile kernels raised
+    bool pipe_attr = false;      // and of the pipeline
     // launch plan of the current tile shape (k_tile_plan), for launches whose
     // tiles all fit the compute units: capacity of one tile per compute unit
     int4* plan = nullptr;
@@ -1004,9 +1005,11 @@ bool pipe_shape(const slbm_ctx* c, Fuse* f)
 
 int pipe_lds_limit(slbm_ctx* c)
 {
+    if (c->pipe_attr) return SLBM_OK;
     for (int k = 0; k < 4; ++k)
         HIPCHK(c, hipFuncSetAttribute(reinterpret_cast<const void*>(pipe_kernel(k & 1, k & 2)),
                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)pipe_lds_bytes<kPipeS>()));
+    c->pipe_attr = true;
     return SLBM_OK;
 }
 

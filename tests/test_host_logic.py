@@ -136,3 +136,27 @@ def test_panel_plans_take_memory_for_rim_tiles_only(stub):
     """)
     panels, tiles = (int(v) for v in out.split())
     assert panels < 0.6 * tiles
+
+
+def test_kernel_attributes_are_set_once_per_context(stub):
+    """Solves after the first set none: pipeline, panels and tiles of plates."""
+    out = run(stub, """
+        def problem(nx, ny, **more):
+            return dict(nx=nx, ny=ny, dx=1 / nx, E=1.0, nu=0.3, target=np.ones((2, ny, nx)), tol=0.0, max_steps=40,
+                        control_kind=S.CTRL_FORCE_NODAL, **more)
+        def plate(nx, ny):
+            cp = I.clamped_plate(nx, ny)
+            p = problem(nx, ny, domain=S.MASKED, node_mask=cp["active"].astype(np.uint8), link_bc=cp["bc"],
+                        link_wall=cp["wall"], link_normal=cp["normal"])
+            return dict(p, dx=cp["dx"])
+        for p in (problem(900, 900), plate(64, 39), plate(400, 240)):
+            ctx = S.solid_lbm_init(p)
+            sets = []
+            for _ in range(2):
+                stub.stub_reset(-1)
+                S.objective_and_grad(ctx, np.ones((2, p["ny"], p["nx"])))
+                sets.append(sum(op == ATTR for op, _, _ in log()))
+            assert sets[0] > 0 and sets[1] == 0, (p["nx"], sets)
+        print("ok")
+    """)
+    assert out.strip() == "ok"
