@@ -304,15 +304,15 @@ void launch_sweep(slbm_ctx* c, bool adjoint, const SweepArgs& a, bool check)
 #undef SL_CASE
 }
 
-// (step, input buffer) of the latest check sweeps of a solve.  The host sees
-// a passing test at most one or two checks after it happened (it reads the
-// device status one chunk of up to kKeep / 4 checks behind), so the passing
-// check is among the last ones; older entries are dropped, which keeps the record from growing with
-// the length of the run.
 // Steps between two polls of the device status, at least: a poll is a copy and
 // an event (about 5 us); a loop that has converged runs on for up to two polls
 // of launches that return at once.
 constexpr int64_t kPollSteps = 64;
+
+// (step, input buffer) of the latest check sweeps of a solve.  The host reads
+// the device status one poll behind, so the passing check is among those of the
+// last two or three polls (at most kPollSteps + 1 in one); older entries are
+// dropped, which keeps the record from growing with the length of the run.
 struct CheckLog {
     static constexpr size_t kKeep = 1024;
     std::deque<std::pair<int64_t, int>> q;
@@ -1225,12 +1225,11 @@ int tangent_loop(slbm_ctx* c, const TangentArgs& base, int64_t* t_out, int* x_ou
     int64_t s = 0;
     bool stopped = false;
     CheckLog checks;
-    const int64_t poll = std::min<int64_t>(K * (CheckLog::kKeep / 4), kPollSteps);
     auto last_report = std::chrono::steady_clock::now();
     HIPCHK(c, hipEventRecord(c->t0, c->stream));
     while (s <= last && !stopped) {
         // a chunk ends before a check; short intervals are polled several at a time
-        int64_t end = use_tol ? std::min(last, ((s + poll) / K + 1) * K - 1) : last;
+        int64_t end = use_tol ? std::min(last, ((s + kPollSteps) / K + 1) * K - 1) : last;
         if (!use_tol && end - s > 4096) end = s + 4095;
         while (s <= end) {
             const bool check = use_tol && s > 0 && s % K == 0;
@@ -1333,12 +1332,11 @@ int run_loop(slbm_ctx* c, bool adjoint, int start, int64_t last, bool use_tol, i
     }
     const int T = fuse.T, TL = fuse.TL;
     CheckLog checks;                              // (step, input buffer) of the latest check sweeps
-    const int64_t poll = std::min<int64_t>(K * (CheckLog::kKeep / 4), kPollSteps);
     int last_in = start;
     auto last_report = std::chrono::steady_clock::now();
     while (s <= last && !stopped) {
         // a chunk ends before a check; short intervals are polled several at a time
-        int64_t end = use_tol ? std::min(last, ((s + poll) / K + 1) * K - 1) : last;
+        int64_t end = use_tol ? std::min(last, ((s + kPollSteps) / K + 1) * K - 1) : last;
         if (!use_tol && end - s > 4096 * T) end = s + 4096 * T - 1;
         while (s <= end) {
             bool check = use_tol && s > 0 && s % K == 0;

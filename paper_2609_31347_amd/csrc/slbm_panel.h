@@ -227,26 +227,21 @@ __device__ __forceinline__ void panel_tile(const PanelArgs& a, int tile, double*
         };
         // rows 1 .. R - 1 first (row R - 1 reads the edge above), row 0 last:
         // the edges' LDS latency is covered by the rows that need none
-        if (R > 1) {
-            const double sb[3] = {o[1][B0], lane_down(o[1][B1]), lane_up(o[1][B2])};
-            double ca[3] = {o[0][A0], lane_up(o[0][A1]), lane_down(o[0][A2])};
+        const double sb[3] = {o[1][B0], lane_down(o[1][B1]), lane_up(o[1][B2])};
+        double ca[3] = {o[0][A0], lane_up(o[0][A1]), lane_down(o[0][A2])};
 #pragma unroll
-            for (int r = 1; r < R; ++r) {
-                const double na[3] = {o[r][A0], lane_up(o[r][A1]), lane_down(o[r][A2])};
-                if (r < R - 1) {
-                    const int t = r + 1 < R ? r + 1 : r;
-                    const double b[3] = {o[t][B0], lane_down(o[t][B1]), lane_up(o[t][B2])};
-                    row(r, ca, b);
-                } else {
-                    row(r, ca, lb);
-                }
-#pragma unroll
-                for (int k = 0; k < 3; ++k) ca[k] = na[k];
+        for (int r = 1; r < R; ++r) {
+            const double na[3] = {o[r][A0], lane_up(o[r][A1]), lane_down(o[r][A2])};
+            if (r < R - 1) {
+                const double b[3] = {o[r + 1][B0], lane_down(o[r + 1][B1]), lane_up(o[r + 1][B2])};
+                row(r, ca, b);
+            } else {
+                row(r, ca, lb);
             }
-            row(0, la, sb);
-        } else {
-            row(0, la, lb);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) ca[k] = na[k];
         }
+        row(0, la, sb);
         if (MASKED && nbt) {
             __syncthreads();
             __syncthreads();
