@@ -187,8 +187,9 @@ struct slbm_ctx {
     int2* pplan = nullptr;
     double* pplan_coef = nullptr;
     int32_t* pplan_n = nullptr;
-    int2* ptiles = nullptr;
-    std::vector<int2> plive;     // by workgroup: a tile with domain nodes, its place in the plan (-1: no boundary nodes)
+    int32_t* ptiles = nullptr;
+    std::vector<int32_t> plive;  // tiles with domain nodes, by workgroup
+    int prims = 0;               // those with boundary nodes
     std::vector<uint8_t> mask;   // plates: node_mask
     int pshape[2] = {-1, 0};     // rows per lane (-1: not looked for yet, 0: no panels), halo
     int64_t nblk = 0;  // blocks of one sweep
@@ -779,6 +780,7 @@ void launch_panel(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, cons
         a.plan_coef = c->pplan_coef;
         a.plan_n = c->pplan_n;
         a.tiles = c->ptiles;
+        a.rims = c->prims;
     }
     hipLaunchKernelGGL(panel_kernel(c->masked, c->efield_on, adjoint, f.R, check), dim3(wgs),
                        dim3(c->masked ? kPlateBlock : kPanelBlock), c->masked ? kPlateLds : 0, c->stream, a);
@@ -787,7 +789,7 @@ void launch_panel(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, cons
 // Tiles of a plate's panel shape that write at least one domain node, in the
 // order of the workgroups that run them.
 struct PlateTiles {
-    std::vector<int2> list;      // tile, number among the rim tiles (-1: an inner tile)
+    std::vector<int32_t> list;
     int rim = 0;      // tiles with boundary nodes in their region
     int most = 0;     // most boundary nodes of a region (halo and periodic copies included)
 };
@@ -825,20 +827,16 @@ PlateTiles plate_tiles(const slbm_ctx* c, int R, int h)
     // Workgroup b runs entry xcd_order(b) of the list, which hands XCD x one run
     // of it.  Each run gets its share of the slow rim tiles first, then of the
     // inner tiles, both contiguous in the grid: no XCD has more rim tiles than
-    // the others, and its last round is made of inner tiles.
+    // the others, and its last round is made of inner tiles.  A rim tile's number
+    // among the rim tiles, its place in the plan, is then xcd_order(b) of their count.
     const size_t n = rim.size() + inner.size(), nr = rim.size();
     out.list.resize(n);
     out.rim = (int)nr;
     size_t ri = 0, ii = 0, at = 0;
     for (size_t x = 0; x < kXcds; ++x) {
         const size_t len = n / kXcds + (x < n % kXcds ? 1 : 0);
-        size_t r = nr / kXcds + (x < nr % kXcds ? 1 : 0);
-        r = std::min(r, len);
-        if (x == kXcds - 1) r = nr - ri;                 // what is left fits: at + len = n
-        for (size_t k = 0; k < len; ++k, ++at) {
-            out.list[at] = k < r ? make_int2(rim[ri], (int)ri) : make_int2(inner[ii], -1);
-            ++(k < r ? ri : ii);
-        }
+        const size_t r = nr / kXcds + (x < nr % kXcds ? 1 : 0);   // at most len: nr <= n
+        for (size_t k = 0; k < len; ++k) out.list[at++] = k < r ? rim[ri++] : inner[ii++];
     }
     return out;
 }
@@ -900,6 +898,7 @@ bool plate_shape(slbm_ctx* c, Fuse* f)
                 c->pshape[0] = R;
                 c->pshape[1] = h;
                 c->plive = std::move(t.list);
+                c->prims = t.rim;
             }
             int tw, th;
             tile_shape(c, tile_halo(c, false), &tw, &th);
@@ -914,12 +913,12 @@ bool plate_shape(slbm_ctx* c, Fuse* f)
     return true;
 }
 
-// Builds the launch plan of a plate's panels for c->plive, once: 66 KiB per tile with boundary nodes.
+// Builds the launch plan of a plate's panels for c->plive, once: 70 KiB per tile with boundary nodes.
 int build_panel_plan(slbm_ctx* c, int R, int h)
 {
     if (c->pplan_n) return SLBM_OK;
     const int64_t wgs = (int64_t)c->plive.size();
-    const int64_t rims = std::count_if(c->plive.begin(), c->plive.end(), [](const int2& t) { return t.y >= 0; });
+    const int64_t rims = c->prims;
     int rc;
     const void* fns[4] = {reinterpret_cast<const void*>(panel_kernel(true, false, false, R)),
                           reinterpret_cast<const void*>(panel_kernel(true, false, true, R)),
@@ -927,8 +926,8 @@ int build_panel_plan(slbm_ctx* c, int R, int h)
                           reinterpret_cast<const void*>(panel_kernel(true, true, true, R))};
     for (const void* fn : fns)
         HIPCHK(c, hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kPlateLds));
-    const size_t bytes[4] = {(size_t)rims * kPanelCap * sizeof(int2), (size_t)rims * kPanelCap * 32 * sizeof(double),
-                             (size_t)wgs * sizeof(int2), (size_t)wgs * sizeof(int32_t)};
+    const size_t bytes[4] = {(size_t)rims * kPanelCap * sizeof(int2), (size_t)rims * kPanelStride * sizeof(double),
+                             (size_t)wgs * sizeof(int32_t), (size_t)wgs * sizeof(int32_t)};
     void* p[4] = {};
     for (int k = 0; k < 4; ++k)
         if ((rc = dalloc(c, &p[k], bytes[k]))) {
@@ -937,15 +936,16 @@ int build_panel_plan(slbm_ctx* c, int R, int h)
         }
     int2* plan = (int2*)p[0];
     double* coef = (double*)p[1];
-    c->ptiles = (int2*)p[2];
+    c->ptiles = (int32_t*)p[2];
     int32_t* count = (int32_t*)p[3];
-    HIPCHK(c, hipMemcpyAsync(c->ptiles, c->plive.data(), (size_t)wgs * sizeof(int2), hipMemcpyHostToDevice,
+    HIPCHK(c, hipMemcpyAsync(c->ptiles, c->plive.data(), (size_t)wgs * sizeof(int32_t), hipMemcpyHostToDevice,
                              c->stream));
     PanelArgs a;
     std::memset(&a, 0, sizeof(a));
     a.code = c->code;
     a.bnodes = c->bnodes;
     a.tiles = c->ptiles;
+    a.rims = c->prims;
     a.nx = c->nx;
     a.ny = c->ny;
     a.halo = h;

@@ -77,17 +77,22 @@ struct PanelArgs {
     const BNode* __restrict__ bnodes;
     double E0;
     // launch plan of the shape (k_panel_plan): by place in the plan, per slot (cell,
-    // cut | dirichlet << 8 | written << 16) and 32 coefficient planes of kPanelCap;
-    // by workgroup, its boundary nodes
+    // cut | dirichlet << 8 | written << 16) and 32 coefficient planes of kPanelCap
+    // (kPanelStride words in all); by workgroup, its boundary nodes
     const int2* __restrict__ plan;
     const double* __restrict__ plan_coef;
     const int32_t* __restrict__ plan_n;
-    const int2* __restrict__ tiles;       // tile of each workgroup, its place in the plan (-1: none)
+    const int32_t* __restrict__ tiles;    // tile of each workgroup
+    int32_t rims;                         // tiles with boundary nodes: the first of every XCD's run
 };
 
 // Boundary nodes that a workgroup takes (plates): kPanelBWaves waves, one node per lane.
 constexpr int kPanelBWaves = 4;
 constexpr int kPanelCap = 64 * kPanelBWaves;
+// Words of a tile's coefficient planes in the plan: not a power of two (64 KiB
+// apart the adjoint's steps of 32-column panels took 4 % longer, the primal's 1.5 %
+// less: 360 x 216 2.23 and 2.27 us, 2.14 and 2.30 so).
+constexpr int kPanelStride = 32 * kPanelCap + 544;
 constexpr int kPlateBlock = 64 * (kPanelWaves + kPanelBWaves);
 
 // Edge rows: 2 parities x waves x 6 populations x 64 columns.
@@ -298,7 +303,7 @@ __device__ __forceinline__ void panel_boundary(const PanelArgs& a, int place, in
     for (int q = 0; q < 8; ++q)
 #pragma unroll
         for (int j = 0; j < (ADJ ? 3 : 4); ++j)
-            bn.coef[q][j] = ldg(a.plan_coef + ((int64_t)place * 32 + 4 * q + j) * kPanelCap + (on ? slot : 0));
+            bn.coef[q][j] = ldg(a.plan_coef + (int64_t)place * kPanelStride + (4 * q + j) * kPanelCap + (on ? slot : 0));
     const int64_t cell = en.x;
     bn.cut = (uint32_t)en.y & 0xffu;
     bn.dirichlet = ((uint32_t)en.y >> 8) & 0xffu;
@@ -374,20 +379,21 @@ __global__ __launch_bounds__(kPlateBlock) void k_sweep_plate(PanelArgs a)
     __shared__ int cnt[kPanelWaves];
     const int wg = xcd_order(blockIdx.x, gridDim.x);
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int2 t = a.tiles[wg];
+    const int tile = a.tiles[wg];
     const int nbt = a.plan_n[wg];
     double2* io = reinterpret_cast<double2*>(lds + kPanelEdge);
-    if (w < kPanelWaves) panel_tile<true, EFIELD, ADJ, R, WC>(a, t.x, lds, io, cnt, nbt);
-    else if (nbt) panel_boundary<EFIELD, ADJ>(a, t.y, w - kPanelWaves, io, nbt);
+    if (w < kPanelWaves) panel_tile<true, EFIELD, ADJ, R, WC>(a, tile, lds, io, cnt, nbt);
+    else if (nbt) panel_boundary<EFIELD, ADJ>(a, xcd_order(blockIdx.x, a.rims), w - kPanelWaves, io, nbt);
 }
 
-// Launch plan of a plate's panels (grid: one workgroup per live tile, in the
-// order of the tile list): the boundary nodes of its region in region order,
-// spread over the boundary waves, with their records in planes, so that a
-// boundary wave loads consecutive words.
+// Launch plan of a plate's panels (grid: that of the sweeps): the boundary nodes
+// of every region in region order, spread over the boundary waves, with their
+// records in planes, so that a boundary wave loads consecutive words.
 __global__ __launch_bounds__(kPanelBlock) void k_panel_plan(PanelArgs a, int R, int cols, int2* plan, double* coef, int32_t* plan_n)
 {
-    const int wg = blockIdx.x, tile = a.tiles[wg].x, place = a.tiles[wg].y, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int b = blockIdx.x, wg = xcd_order(b, gridDim.x), tile = a.tiles[wg], lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int place = xcd_order(b, a.rims);
+    const bool rim = b / kXcds < a.rims / kXcds + (b % kXcds < a.rims % kXcds ? 1 : 0);
     const int h = a.halo, HW = 64 / cols, RY = kPanelWaves * HW * R;
     const int x0 = (tile % a.tiles_x) * (cols - 2 * h) - h, y0 = (tile / a.tiles_x) * (RY - 2 * h) - h;
     const int col = lane % cols, row0 = (w * HW + lane / cols) * R;
@@ -410,15 +416,15 @@ __global__ __launch_bounds__(kPanelBlock) void k_panel_plan(PanelArgs a, int R, 
         const uint64_t b = __ballot(code > 0);
         const int e = at + __popcll(b & __lanemask_lt());
         const bool wr = colin && ry >= h && ry < RY - h && y0 + ry < a.ny;
-        if (code > 0 && place >= 0 && e < kPanelCap) {
+        if (code > 0 && rim && e < kPanelCap) {
             const BNode& bn = a.bnodes[code - 1];
             const int s = panel_slot(e);
             plan[(int64_t)place * kPanelCap + s] = make_int2((int)n, (int)(bn.cut | bn.dirichlet << 8 | (wr ? 1u << 16 : 0u)));
-            for (int k = 0; k < 32; ++k) coef[((int64_t)place * 32 + k) * kPanelCap + s] = bn.coef[k / 4][k % 4];
+            for (int k = 0; k < 32; ++k) coef[(int64_t)place * kPanelStride + k * kPanelCap + s] = bn.coef[k / 4][k % 4];
         }
         at += __popcll(b);
     }
-    if (threadIdx.x == 0) plan_n[wg] = place >= 0 ? min(total, kPanelCap) : 0;
+    if (threadIdx.x == 0) plan_n[wg] = rim ? min(total, kPanelCap) : 0;
 }
 
 }  // namespace slbm
