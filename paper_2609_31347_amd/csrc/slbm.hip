@@ -176,6 +176,7 @@ struct slbm_ctx {
     double progress_every = 0.0;          // seconds between reports
     bool tile_attr = false;      // LDS limits of the plate tile kernels raised
     bool pipe_attr = false;      // and of the pipeline
+    bool flags_clear = false;    // no flag of the control check is set
     // launch plan of the current tile shape (k_tile_plan), for launches whose
     // tiles all fit the compute units: capacity of one tile per compute unit
     int4* plan = nullptr;
@@ -1073,7 +1074,7 @@ void launch_region(slbm_ctx* c, bool adjoint, const SweepArgs& s, int steps, con
 // ---------------------------------------------------------------- tangent solves
 int64_t control_len(const slbm_ctx* c);
 int means_device(slbm_ctx* c, const double* a, const double** means);
-int check_control_device(slbm_ctx* c, const double* control, int64_t len, const char* what);
+int check_control_device(slbm_ctx* c, const double* control, int64_t len, const char* what, double* value);
 
 int tangent_buffers(slbm_ctx* c)
 {
@@ -1100,9 +1101,9 @@ int tangent_direction(slbm_ctx* c, const double* dir, int ptr_kind, bool* use_gd
     if (!dir) return fail(c, SLBM_EINVAL, "direction is NULL");
     const bool field = c->kind == SLBM_CTRL_FORCE_NODAL || c->kind == SLBM_CTRL_E_NODAL;
     const bool on_device = field && ptr_kind == SLBM_PTR_DEVICE;
-    std::vector<double> h(on_device ? 0 : len);
+    std::vector<double> h(on_device ? 1 : len);
     if (on_device) {
-        int rc = check_control_device(c, dir, len, "direction");
+        int rc = check_control_device(c, dir, len, "direction", h.data());
         if (rc) return rc;
     } else if (ptr_kind == SLBM_PTR_DEVICE) {
         HIPCHK(c, hipMemcpyAsync(h.data(), dir, len * sizeof(double), hipMemcpyDeviceToHost, c->stream));
@@ -1493,17 +1494,19 @@ int means_device(slbm_ctx* c, const double* a, const double** means)
 }
 
 // Tests a control (or, with what = "direction", its derivative) in device
-// memory before anything changes; one small read-back.
-int check_control_device(slbm_ctx* c, const double* control, int64_t len, const char* what)
+// memory before anything changes, and reads its first entry; one small read-back.
+// The flags are set only by a control that fails, so they are reset after one.
+int check_control_device(slbm_ctx* c, const double* control, int64_t len, const char* what, double* value)
 {
     const bool moduli = c->kind == SLBM_CTRL_E_NODAL && std::strcmp(what, "control") == 0;
     unsigned long long* flags = reinterpret_cast<unsigned long long*>(c->scal + kScalFlags);
-    hipLaunchKernelGGL(k_control_reset, dim3(1), dim3(64), 0, c->stream, flags);
+    if (!c->flags_clear) hipLaunchKernelGGL(k_control_reset, dim3(1), dim3(64), 0, c->stream, flags);
+    c->flags_clear = false;
     const unsigned blocks = (unsigned)std::min<int64_t>((len + kBlock - 1) / kBlock, 4096);
     hipLaunchKernelGGL(k_control_check, dim3(blocks), dim3(kBlock), 0, c->stream, control, len, moduli ? 1 : 0,
                        c->masked ? 1 : 0, c->nu, flags);
     HIPCHK(c, hipGetLastError());
-    unsigned long long first[3];
+    unsigned long long first[4];
     HIPCHK(c, hipMemcpyAsync(first, flags, sizeof(first), hipMemcpyDeviceToHost, c->stream));
     HIPCHK(c, hipStreamSynchronize(c->stream));
     if (first[CTL_NONFINITE] != ~0ull)
@@ -1512,6 +1515,8 @@ int check_control_device(slbm_ctx* c, const double* control, int64_t len, const 
         return fail(c, SLBM_EINVAL, "E control must be > 0 everywhere");
     if (moduli && first[CTL_GAMMA] != ~0ull)
         return fail(c, SLBM_EINVAL, "tau_s = tau_f: the boundary coefficient gamma is undefined");
+    c->flags_clear = true;
+    std::memcpy(value, first + CTL_VALUE, sizeof(double));
     return SLBM_OK;
 }
 
@@ -1552,12 +1557,11 @@ int apply_control(slbm_ctx* c, const double* control, int ptr_kind)
     const bool field = c->kind == SLBM_CTRL_FORCE_NODAL || c->kind == SLBM_CTRL_E_NODAL;
     const bool on_device = field && ptr_kind == SLBM_PTR_DEVICE;
     std::vector<double> h(on_device ? 1 : len);
-    if (ptr_kind == SLBM_PTR_DEVICE) {
-        HIPCHK(c, hipMemcpyAsync(h.data(), control, h.size() * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-        if (on_device) {
-            int rc = check_control_device(c, control, len, "control");
-            if (rc) return rc;
-        }
+    if (on_device) {
+        int rc = check_control_device(c, control, len, "control", h.data());
+        if (rc) return rc;
+    } else if (ptr_kind == SLBM_PTR_DEVICE) {
+        HIPCHK(c, hipMemcpyAsync(h.data(), control, len * sizeof(double), hipMemcpyDeviceToHost, c->stream));
         HIPCHK(c, hipStreamSynchronize(c->stream));
     } else {
         std::memcpy(h.data(), control, len * sizeof(double));

@@ -306,10 +306,11 @@ __global__ __launch_bounds__(kBlock) void k_sum_partials(const double* __restric
 
 // First index of a control array (device memory) that is not finite, is not a
 // positive modulus, or makes the boundary coefficient gamma undefined (kinds 0,
-// 1, 2 of `first`; ~0 = none; the last two for modulus controls only).  The
+// 1, 2 of `first`; ~0 = none; the last two for modulus controls only), and its
+// first entry (CTL_VALUE).  The
 // host used to copy the whole control back for these tests: 20 of 185 ms of a
 // 2048^2 gradient of 4096 + 4096 steps.
-enum { CTL_NONFINITE = 0, CTL_NONPOSITIVE = 1, CTL_GAMMA = 2 };
+enum { CTL_NONFINITE = 0, CTL_NONPOSITIVE = 1, CTL_GAMMA = 2, CTL_VALUE = 3 };
 __global__ void k_control_reset(unsigned long long* first)
 {
     if (threadIdx.x < 3) first[threadIdx.x] = ~0ull;
@@ -318,6 +319,7 @@ __global__ __launch_bounds__(kBlock) void k_control_check(const double* __restri
                                                          double nu, unsigned long long* first)
 {
     const int64_t step = (int64_t)gridDim.x * kBlock;
+    if (blockIdx.x == 0 && threadIdx.x == 0) first[CTL_VALUE] = (unsigned long long)__double_as_longlong(a[0]);
     for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n; i += step) {
         const double v = a[i];
         if (!isfinite(v)) atomicMin(first + CTL_NONFINITE, (unsigned long long)i);
