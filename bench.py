@@ -39,7 +39,7 @@ PEAK_GBS = 8000.0           # MI355X HBM3E
 # plain copy of one population buffer reads in the same runs), mean per
 # dispatch of the fused primal sweep, with the hash of the kernel code they
 # were taken with (kernel_source_hash; profiles/k_sweep_pipe_periodic_2048_bench.md).
-TRAFFIC = {(2048, 16, 0): {"bytes": (2.0 * 201735.0 + 262144.0) * 1024, "sources": "6d3939dcd6e15c82"}}
+TRAFFIC = {(2048, 16, 0): {"bytes": (2.0 * 201735.0 + 262144.0) * 1024, "sources": "0aa5b6a9415e9e33"}}
 
 
 def parse():
@@ -776,8 +776,9 @@ def main():
                              "once and written once, its 2 forcing values read once: 144 B per node per launch) "
                              "/ the launch's average duration from HIP events on the library stream over the "
                              "timed steps; traffic = HBM bytes per launch from rocprofv3 FETCH_SIZE / WRITE_SIZE "
-                             "scaled by a plain copy's factors; launches of 16 steps are bound by FP64 issue at "
-                             "the clock that their power leaves, not by HBM"},
+                             "scaled by a plain copy's factors; 'bound' names the roofline that the metric is "
+                             "quoted on (HBM) -- what limits launches of 16 steps is FP64 issue at the clock that "
+                             "their power leaves"},
         "tuning": {"T": T, "H": H, "tiles": [tw, th], "cached": tune["cached"], "candidates_us": tune.get("us")},
     }
     if tnote:

@@ -273,20 +273,29 @@ int solid_lbm_time_sweeps(slbm_ctx *ctx, int32_t adjoint, int64_t n, double *ms)
  * 1 = one time step per launch, else that many time steps fused in one
  * launch: 2, 4, 6 or 8 for periodic, uniform-material problems (wave-strip
  * kernel), 2 .. 8 for plates, E-field controls and problems given a tile by
- * solid_lbm_set_tiles (LDS-tiled kernel).  Automatic: plates whose 16 x 16
- * tiles fit the compute units at once the LDS-tiled kernel with 8 steps; larger
- * plates register panels of 64 columns (6, 8 or 10 steps, by a model of the
- * launch; a plate whose rim is too dense for them the LDS tiles: 8 steps up to
- * 131072 nodes, above the most of 6, 5, 4, 3 whose (32 - 2 steps)^2 tiles number
- * no more than the compute units, else 6); periodic grids register panels (6 ..
- * 14 steps) while a shape of them fits the compute units at once, and, with a
- * uniform material, a pipeline of 8 waves with 16 steps beyond (fewer steps
- * before a check: wave strips; all wave strips of 8 steps if rows_per_wave is
- * set; thin grids LDS tiles or wave strips).  tangent_solve runs one step per
- * launch with 0 or 1, else tiles of its own (3, 5 or 7 steps) where they pay.  rows_per_wave: rows each
- * wave of a wave-strip launch covers (0 = automatic: as many as keep the wave
- * count at or below the device's SIMD count).  Every setting gives the same result bit for bit:
- * a fused launch performs exactly the arithmetic of its single sweeps.
+ * solid_lbm_set_tiles (LDS-tiled kernel).  Automatic:
+ *  - plates whose 16 x 16 tiles fit the compute units at once: LDS tiles of 8
+ *    steps (the check interval instead if that is 9 .. 12 and 8 x 8 tiles fit at
+ *    once); larger plates: register panels of 32 or 64 columns, 6, 8 or 10 steps
+ *    by a model of the launch, unless that is slower than LDS tiles or a rim is
+ *    too dense for them;
+ *  - periodic grids: register panels while a shape of them fits the compute
+ *    units at once: 32 columns with 14 .. 6 steps (as few as 4 where checks come
+ *    that often), else 64 columns with 6 .. 12; beyond, uniform materials a
+ *    pipeline of 8 waves with 16 steps (fewer steps before a check: wave strips;
+ *    strips of 8 steps on flat grids, and above 131072 nodes if rows_per_wave is
+ *    set), E fields panels of 6 steps or, on narrow grids, LDS tiles;
+ *  - LDS tiles by themselves: 8 steps up to 131072 nodes, above the most of 6, 5,
+ *    4, 3 whose (32 - 2 steps)^2 tiles number no more than the compute units,
+ *    else 6.
+ * tangent_solve runs one step per launch with 0 or 1, else tiles of its own (3,
+ * 5 or 7 steps) where they pay.  rows_per_wave: rows each wave of a wave-strip
+ * launch covers (0 = automatic: as many as keep the wave count at or below the
+ * device's SIMD count).  A fused launch performs exactly the arithmetic of its
+ * single sweeps, so after the same number of steps every setting gives the same
+ * populations, fields and gradients bit for bit.  Residuals are summed in an
+ * order that depends on the launch shape and can differ by rounding: a solve
+ * whose residual comes that close to tol can stop one check earlier or later.
  * SLBM_EINVAL if the value is out of range, or if a tile set by
  * solid_lbm_set_tiles would not fit with a halo of steps_per_launch. */
 int solid_lbm_set_tuning(slbm_ctx *ctx, int32_t steps_per_launch, int32_t rows_per_wave);
@@ -296,7 +305,8 @@ int solid_lbm_set_tuning(slbm_ctx *ctx, int32_t steps_per_launch, int32_t rows_p
  * tile plus a halo of
  * steps_per_launch nodes on every side must hold at most 1024 nodes (one
  * node per thread of a 1024-thread workgroup; 8 FP64 planes in 64 KiB of
- * LDS, two copies for plates).  0, 0 = automatic (a 32 x 32 region; with
+ * LDS, two copies for plates); with automatic steps the halo is the automatic
+ * one, at most 8.  0, 0 = automatic (a 32 x 32 region; with
  * 8 steps per launch, grids that 16 x 16 tiles would leave short of one
  * workgroup per compute unit take 8 x 8 or 12 x 12 tiles).  Shapes whose
  * tiles all fit the device's compute units run with a launch plan (each
@@ -331,12 +341,14 @@ void solid_lbm_destroy(slbm_ctx *ctx);
 /* ---- batches: many independent problems solved together ----
  *
  * A batch holds up to 128 problems of any sizes and kinds (periodic or plate,
- * any control) that share tol, max_steps and stream.  All of them
- * advance in the same launches: one launch per time step (or per T fused
- * steps for the periodic ones) covers every instance still running, each with
- * its own residual test every K_i steps and its own stop.  Results equal those
- * of the same problems solved one by one (the per-instance arithmetic is the
- * same). */
+ * any control) that share tol, max_steps and stream.  All of them advance in
+ * shared launches, in two classes (wave strips: periodic problems of uniform
+ * material; LDS tiles: plates and E fields); with both present the tiled class
+ * runs on a stream of the library's own, ordered before and after the solve with
+ * the batch's.  Every instance has its own step counter, its own residual test
+ * every K_i steps and its own stop.  Results equal those of the same problems
+ * solved one by one (the per-instance arithmetic is the same; for residuals
+ * within rounding of tol see solid_lbm_set_tuning). */
 typedef struct slbm_batch slbm_batch;
 
 /* Creates a batch from count problems (validated and copied as by

@@ -1954,6 +1954,7 @@ int solid_lbm_init(const slbm_problem* p, slbm_ctx** out)
     c->normalize = p->normalize_objective ? 1 : 0;
     c->masked = masked;
     c->nb = (int)bn.size();
+    c->bcells.reserve(bn.size());
     for (const BNode& b : bn) c->bcells.push_back(b.cell);
     if (masked) c->mask.assign(p->node_mask, p->node_mask + N);
     c->stream = (hipStream_t)p->stream;

@@ -1284,7 +1284,7 @@ __device__ __forceinline__ void block_sum2_tile(double a, double b, double* out)
 // sweeps, over the tile's own nodes); on grids this small a check as a
 // launch of its own, the single step that then stays over and a status copy per
 // check took half the time of a solve that checks every 10 steps (64 x 39
-// plate, 4000 + 4000 steps: 26.4 ms, 16.4 with the checks in fused launches and
+// plate, 4000 + 4000 steps: 26.4 ms, 16.2 with the checks in fused launches and
 // a poll every 64 steps).  Handing the sums to the workgroup that arrives last,
 // instead of a launch for the residual, took 7 % longer there.
 template <bool MASKED, bool EFIELD, bool ADJ, bool PLAN = false, bool CHECK = false>
