@@ -1,17 +1,18 @@
 /* A HIP runtime for tests of the library's host side without a GPU: device
  * memory is host memory, copies are memcpy, kernels do not run.  Launches,
- * waits, attribute settings and allocations are logged in order with their
- * stream (device, bytes), and one launch can be made to fail. */
+ * waits, attribute settings, allocations and copies to the host are logged in
+ * order with their stream (device, bytes); one launch can be made to fail, and
+ * the byte that new memory holds can be set. */
 #include <stdlib.h>
 #include <string.h>
 
 typedef struct { unsigned x, y, z; } dim3;
 typedef void *stream_t;
-enum { LAUNCH = 1, SYNC = 2, ATTR = 3, ALLOC = 4 };
+enum { LAUNCH = 1, SYNC = 2, ATTR = 3, ALLOC = 4, READ = 5 };
 enum { SUCCESS = 0, FAILED = 719 };
 
 static struct { int op; const void *what, *where; } entries[1 << 20];
-static int n_log, device, error, fail_at = -1, n_launch;
+static int n_log, device, error, fail_at = -1, n_launch, fill;
 static struct { dim3 grid, block; size_t lds; stream_t stream; } call;
 
 static void put(int op, const void *what, const void *where)
@@ -26,6 +27,7 @@ static void put(int op, const void *what, const void *where)
 /* control by the tests */
 void stub_reset(int fail) { n_log = n_launch = error = 0; fail_at = fail; }
 void stub_device(int d) { device = d; }
+void stub_fill(int byte) { fill = byte; }
 int stub_size(void) { return n_log; }
 int stub_op(int i) { return entries[i].op; }
 const void *stub_what(int i) { return entries[i].what; }
@@ -78,12 +80,12 @@ int hipFuncSetAttribute(const void *f, int what, int v) { (void)what, (void)v; p
 int hipFuncGetAttributes(void *a, const void *f) { (void)a, (void)f; return FAILED; }
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *f, int b, size_t l) { (void)f, (void)b, (void)l; *n = 1; return SUCCESS; }
 int hipGetSymbolAddress(void **p, const void *s) { (void)s; *p = 0; return FAILED; }
-int hipMalloc(void **p, size_t n) { put(ALLOC, (void *)n, 0); *p = calloc(n, 1); return *p ? SUCCESS : 2; }
+int hipMalloc(void **p, size_t n) { put(ALLOC, (void *)n, 0); *p = malloc(n); if (*p) memset(*p, fill, n); return *p ? SUCCESS : 2; }
 int hipFree(void *p) { free(p); return SUCCESS; }
 int hipHostMalloc(void **p, size_t n, unsigned f) { (void)f; return hipMalloc(p, n); }
 int hipHostFree(void *p) { free(p); return SUCCESS; }
 int hipMemcpy(void *d, const void *s, size_t n, int k) { (void)k; memmove(d, s, n); return SUCCESS; }
-int hipMemcpyAsync(void *d, const void *s, size_t n, int k, stream_t st) { (void)k, (void)st; memmove(d, s, n); return SUCCESS; }
+int hipMemcpyAsync(void *d, const void *s, size_t n, int k, stream_t st) { if (k == 2) put(READ, (void *)n, st); memmove(d, s, n); return SUCCESS; }
 int hipMemset(void *d, int v, size_t n) { memset(d, v, n); return SUCCESS; }
 int hipStreamCreateWithFlags(stream_t *s, unsigned f) { (void)f; *s = malloc(1); return SUCCESS; }
 int hipStreamDestroy(stream_t s) { free(s); return SUCCESS; }

@@ -1,5 +1,5 @@
 """The library's host side on a stubbed HIP runtime (hip_stub.c; no GPU): waits
-after a failed launch, kernel attributes of every device, memory of launch plans."""
+after a failed launch, kernel attributes of every device, memory of launch plans, which kernels are chosen."""
 import os
 import subprocess
 import sys
@@ -19,9 +19,13 @@ for f in ("stub_what", "stub_where"):
 sys.path.insert(0, {root!r})
 import numpy as np
 from paper_2609_31347_amd import inputs as I, slbm as S
-LAUNCH, SYNC, ATTR, ALLOC = 1, 2, 3, 4
+LAUNCH, SYNC, ATTR, ALLOC, READ = 1, 2, 3, 4, 5
 def log():
     return [(stub.stub_op(i), stub.stub_what(i), stub.stub_where(i)) for i in range(stub.stub_size())]
+def kernels(call):
+    stub.stub_reset(-1)
+    call()
+    return [what for op, what, _ in log() if op == LAUNCH]
 """
 
 
@@ -159,4 +163,87 @@ def test_kernel_attributes_are_set_once_per_context(stub):
             assert sets[0] > 0 and sets[1] == 0, (p["nx"], sets)
         print("ok")
     """)
+    assert out.strip() == "ok"
+
+
+@pytest.mark.parametrize("nx,ny,tiles", [(60, 5000, True), (60, 8000, True), (40, 4000, False), (400, 240, False)])
+def test_narrow_plates_run_in_lds_tiles(stub, nx, ny, tiles):
+    """Columns whose width suits no panel shape launch the kernels that an explicit
+    6 steps per launch does (LDS tiles); others have panels."""
+    out = run(stub, f"nx, ny, tiles = {nx}, {ny}, {tiles}" + """
+cp = I.clamped_plate(nx, ny, b=(ny - 5.0) / (nx - 4.0) if ny > nx else 0.6)
+p = dict(nx=nx, ny=ny, dx=cp["dx"], E=1.0, nu=0.3, domain=S.MASKED, node_mask=cp["active"].astype(np.uint8),
+         link_bc=cp["bc"], link_wall=cp["wall"], link_normal=cp["normal"], target=np.ones((2, ny, nx)), tol=0.0,
+         max_steps=48, control_kind=S.CTRL_FORCE_NODAL)
+ctx = S.solid_lbm_init(p)
+used = []
+for tuning in (6, -1):
+    S.solid_lbm_set_tuning(ctx, tuning, 0)
+    S.objective_and_grad(ctx, np.ones((2, ny, nx)))               # builds the launch plan
+    used.append(set(kernels(lambda: S.objective_and_grad(ctx, np.ones((2, ny, nx))))))
+assert (used[0] == used[1]) == tiles
+print("ok")
+""")
+    assert out.strip() == "ok"
+
+
+@pytest.mark.parametrize("nx,ny,steps", [(3, 20000, 1), (100000, 3, 1), (17, 20000, 1), (3, 4000, 3), (96, 96, 7),
+                                         (600, 600, 3)])
+def test_tangent_launches(stub, nx, ny, steps):
+    """Tiles of several tangent steps, single steps on thin grids, and single steps
+    wherever the caller set one step per launch."""
+    out = run(stub, f"nx, ny, steps = {nx}, {ny}, {steps}" + """
+F = np.ones((2, ny, nx))
+ctx = S.solid_lbm_init(dict(nx=nx, ny=ny, dx=1 / nx, E=1.0, nu=0.3, target=F, fixed_force=F, tol=0.0, max_steps=210,
+                            control_kind=S.CTRL_E_SCALAR_SQ))
+one = np.array([1.0])
+def launches(tuning):
+    S.solid_lbm_set_tuning(ctx, tuning, 0)
+    return kernels(lambda: S.tangent_solve(ctx, one, one))
+single, auto = launches(1), launches(-1)
+assert len(single) >= 210
+assert len(single) - len(auto) == (210 - 210 // steps)
+assert (set(single) == set(auto)) == (steps == 1)
+print("ok")
+""")
+    assert out.strip() == "ok"
+
+
+@pytest.mark.parametrize("B,H,W,dil,memory", [(32, 39, 64, 8, True), (32, 39, 64, 4, False), (4, 39, 64, 8, False),
+                                              (32, 512, 1, 1, True), (64, 256, 10, 2, True), (32, 200, 20, 1, False)])
+def test_form_of_the_forward_convolution(stub, B, H, W, dil, memory):
+    """From memory where staging the tiles' regions costs more: the kernel is that of
+    a dilation whose region cannot be staged at all."""
+    out = run(stub, f"B, H, W, dil, memory = {B}, {H}, {W}, {dil}, {memory}" + """
+P = ctypes.c_void_p
+p = P(ctypes.addressof((ctypes.c_char * 64)()))
+def call(d):
+    return kernels(lambda: S.LIB.slbm_conv3x3_forward(p, p, p, p, None, B, 32, 32, H, W, 0, d, None))
+assert len(call(dil)) == 1
+assert (call(dil) == call(60)) == memory
+print("ok")
+""")
+    assert out.strip() == "ok"
+
+
+@pytest.mark.parametrize("kind", ["E", "force"])
+def test_device_controls_are_tested_with_one_launch_and_one_read(stub, kind):
+    """New memory holds all ones, so no flag of the test is set."""
+    out = run(stub, f"kind = {kind!r}" + """
+stub.stub_fill(255)
+n = 24
+F = np.ones((2, n, n))
+ctx = S.solid_lbm_init(dict(nx=n, ny=n, dx=1 / n, E=1.0, nu=0.3, target=F, fixed_force=F, tol=0.0, max_steps=4,
+                            zero_mean_projection=0, control_kind=S.CTRL_E_NODAL if kind == "E" else S.CTRL_FORCE_NODAL))
+c = F[0].copy() if kind == "E" else F
+def counts(where):
+    stub.stub_reset(-1)
+    assert S.LIB.solid_lbm_set_control(ctx.handle, ctypes.c_void_p(c.ctypes.data), None, where) == 0
+    ops = [op for op, _, _ in log()]
+    return ops.count(LAUNCH), ops.count(READ)
+counts(S.PTR_DEVICE)                                               # the first resets the flags
+host, device = counts(S.PTR_HOST), counts(S.PTR_DEVICE)
+assert host[1] == 0 and device == (host[0] + 1, 1), (host, device)
+print("ok")
+""")
     assert out.strip() == "ok"
